@@ -318,6 +318,69 @@ struct CoarseSolve {
 };
 template <class T>
 void launch_coarse_solve(const CoarseSolve &cs, const T *x, T *y, hipStream_t s, int ncol = 1);
+
+// ---------------------------------------------------------------- subtree.hip
+// The last levels of a hierarchy, small enough that one workgroup holds all of their
+// matrices (in registers) and vectors (in LDS) together: the coarse correction of the
+// top one (its nu flexible-CG steps and everything below them) is one launch.
+// lev[0] is the coarsest level of the hierarchy, lev[levels - 1] the top one.
+constexpr int kSubtreeThreads = 512;
+constexpr int kSubtreeDepth = 6;        // levels above the coarsest one
+constexpr int kSubtreeMaxRows = 4096;   // rows of a level that may be tried
+// Lane slots of a level: slot s of wavefront slot s / 64, which is slot k = s / 512 of
+// thread s % 512 (see SubRow in subtree.h).
+struct SubSlots {
+    int count;
+    const void *va, *minv;  // type T; entry u of slot s at u * count + s
+    const int2 *ci;
+    const int *ig, *sbe, *agg;
+};
+struct SubLevel {
+    int n;
+    int waves;               // wavefront slots
+    int nover;               // of them, rows longer than their lanes hold (the first ones)
+    int optr, ova, oci;      // LDS bytes: the long rows' other entries (starts, values T, 16-bit columns)
+    SubSlots slots;
+};
+struct Subtree {
+    int levels = 0;          // 0: none
+    int width = 1;           // slots per thread on the top level (1, 2 or 4; one on the others)
+    int nu = 2;
+    int lds_bytes = 0, over_at = 0, over_bytes = 0;  // the long rows' entries: LDS offset, image size
+    int m = 0, nd = 0;       // exact solve: coupled and decoupled unknowns (see CoarseSolve)
+    const double *exact_ainv = nullptr, *exact_dinv = nullptr;
+    const int *exact_index = nullptr;
+    const void *over = nullptr;
+    SubLevel lev[kSubtreeDepth + 1];
+};
+struct SubtreeSource {  // the level arrays that the slots are packed from (solve layout, values of type T)
+    struct Lev {
+        int n;
+        const int *rp, *ci, *agg, *seg;
+        const void *va, *minv;
+    } lev[kSubtreeDepth + 1];
+    CoarseSolve cs;
+};
+// What a level needs: wavefront slots, long rows and their entries past the slots.
+struct SubtreeNeed {
+    int waves, nover, over;
+};
+int subtree_lds_limit();
+// need[d], d = 1 .. count - 1 (device array) of the `count` last levels
+void launch_subtree_needs(const SubtreeSource &P, int count, SubtreeNeed *need, hipStream_t s);
+// The deepest subtree that fits (levels >= 2 in S), from the needs of the `count`
+// last levels (n: their sizes, coarsest first).  S's arrays are taken from alloc(bytes).
+bool layout_subtree(int count, const int *n, const SubtreeNeed *need, const CoarseSolve &cs, int value_bytes,
+                    int lds_limit, Subtree &S);
+size_t subtree_bytes(const Subtree &S, int value_bytes);
+// Sets S's array pointers into `base` (subtree_bytes) and fills the arrays.
+template <class T>
+void launch_subtree_pack(Subtree &S, const SubtreeSource &P, void *base, hipStream_t s);
+// e = the coarse correction of the subtree's top level for its restricted residual rc.
+// theta2 > 0: the squared K-cycle threshold.
+template <class T>
+void launch_subtree(const Subtree &S, const T *rc, T *e, int *flag, hipStream_t s, int ncol = 1,
+                    const int *gate = nullptr, double theta2 = 0.0);
 // r32 = r / sqrt(rr[c * kScalCol]) (FP32); z = sqrt(rr[c * kScalCol]) z32 with the
 // partials of (z, q)
 void launch_to_inner(int n, const double *r, const double *rr, float *r32, hipStream_t s, int ncol = 1);

@@ -317,6 +317,9 @@ struct amg_hierarchy {
     std::vector<Level> lev;
     double *ainv = nullptr;  // dense inverse of the coarsest matrix (of its coupled block when split)
     amg::CoarseSolve coarse{};  // the coarsest level's exact solve
+    // the levels from sub_top on, served by one workgroup in LDS (sub_top 0: none)
+    amg::Subtree sub{};
+    int sub_top = 0;
     // outer iteration vectors (finest level, solve layout)
     double *b = nullptr, *x = nullptr, *r = nullptr, *z = nullptr, *p = nullptr, *q = nullptr;
     DotBuf d_pq{}, d_rr{}, d_zq{}, d_res{};
@@ -328,6 +331,7 @@ struct amg_hierarchy {
     bool mixed = false;       // FP32 K-cycle inside the FP64 outer iteration
     float *r32 = nullptr, *z32 = nullptr;
     KDots kd0{};             // dots of the finest visit's coarse correction (for timing)
+    int mode0 = -1;          // how its post-smoothing takes the correction (-1: no K-cycle yet)
     int *flag = nullptr;     // bit 0: Krylov breakdown
     struct Graphs {
         hipGraphExec_t k = nullptr, step = nullptr;
@@ -465,6 +469,7 @@ struct amg_hierarchy {
     void build(const amg_csr &A);
     void finalize_layout();
     void build_sell(int l, const int *rp, const int *ci, const double *va);
+    void build_subtree();
     // the inner residual rt = rcf - (alpha1/rho1) v1 of a parent's first step
     template <class T>
     struct RtSource {
@@ -964,6 +969,7 @@ void amg_hierarchy::finalize_layout()
         r32 = pool.alloc<float>((size_t)lev[0].n * nr);
         z32 = pool.alloc<float>((size_t)lev[0].n * nr);
     }
+    build_subtree();
     const int n = lev[0].n;
     b = pool.alloc<double>((size_t)n * nr);
     x = pool.alloc<double>((size_t)n * nr);
@@ -985,6 +991,47 @@ void amg_hierarchy::finalize_layout()
     pool.release(tmp);
     pool.release(scan_tmp);
     for (void *p : drained) pool.release(p);
+}
+
+// The longest run of last levels (not the finest) that one workgroup can hold: every
+// level more halves the launches of a K-cycle.
+void amg_hierarchy::build_subtree()
+{
+    using namespace amg;
+    const int L = levels() - 1;
+    if (L < 2) return;
+    SubtreeSource P{};
+    P.cs = coarse;
+    std::vector<int> n{lev[L].n};  // coarsest first
+    for (int l = L - 1; l >= 1 && L - l <= kSubtreeDepth && lev[l].n <= kSubtreeMaxRows; l--) {
+        const Level &F = lev[l];
+        P.lev[L - l] = SubtreeSource::Lev{F.n, F.rp, F.ci, F.agg_pos, F.seg_ptr, F.va, F.minv};
+        if (mixed) {
+            P.lev[L - l].va = F.k32.va;
+            P.lev[L - l].minv = F.k32.minv;
+        }
+        n.push_back(F.n);
+    }
+    const int count = (int)n.size();
+    if (count < 2) return;
+    if (pool.budget && pool.used + sizeof(SubtreeNeed) * (kSubtreeDepth + 1) > pool.budget) return;
+    SubtreeNeed *dneed = pool.alloc<SubtreeNeed>(kSubtreeDepth + 1);
+    launch_subtree_needs(P, count, dneed, stream);
+    SubtreeNeed need[kSubtreeDepth + 1];
+    to_host(need, dneed, kSubtreeDepth + 1);
+    pool.release(dneed);
+    if (!layout_subtree(count, n.data(), need, coarse, mixed ? 4 : 8, subtree_lds_limit(), sub)) return;
+    const size_t bytes = subtree_bytes(sub, mixed ? 4 : 8);
+    if (pool.budget && pool.used + bytes > pool.budget) return;
+    sub.nu = opt.kcycle_inner;
+    char *base = pool.alloc<char>(bytes);
+    if (mixed) launch_subtree_pack<float>(sub, P, base, stream);
+    else launch_subtree_pack<double>(sub, P, base, stream);
+    sub_top = L + 1 - sub.levels;
+    AMG_TRACE_MSG("levels %d to %d in one workgroup (%d slots per thread, %d bytes of LDS)", sub_top, L, sub.width,
+                  sub.lds_bytes);
+    for (int d = 1; d < count; d++)
+        AMG_TRACE_MSG("level %d: %d rows in %d wavefront slots, %d long", L - d, n[d], need[d].waves, need[d].nover);
 }
 
 // Sliced ELLPACK copies of the levels of at least kSmallLevel rows (not the last
@@ -1067,7 +1114,8 @@ DotRef amg_hierarchy::kcycle(int k, const T *rr, T *xx, const T *wdot, const RtS
     // C small with a single unknown below: the whole coarse correction in one block,
     // which forms (om, rc) itself
     const bool tail = C.tail.n > 0;
-    const double *om = tail ? nullptr : C.omega;
+    const bool subtree = sub_top > 0 && k + 1 == sub_top;  // C and all below it in one launch
+    const double *om = tail || subtree ? nullptr : C.omega;
     if (rts) {  // rr = rt is formed here from the parent's first inner step (never with a threshold)
         C.om_rc = launch_restrict_rt<T>(F.S, F.n, F.sci, FK.wv, rts->rcf, rts->v1, rts->kd, const_cast<T *>(rr),
                                         CK.rc, flag, F.Gs, stream, om, C.d_om, ncol, gate);
@@ -1082,7 +1130,11 @@ DotRef amg_hierarchy::kcycle(int k, const T *rr, T *xx, const T *wdot, const RtS
     int mode;
     const T *edirect = nullptr;
     const int *second = nullptr;  // gate of the second inner step (threshold only)
-    if (tail) {
+    if (subtree) {
+        launch_subtree<T>(sub, CK.rc, CK.c1, flag, stream, ncol, gate, theta * theta);
+        mode = 0;
+        edirect = CK.c1;
+    } else if (tail) {
         const T *tva;
         if constexpr (std::is_same<T, double>::value) tva = C.tail_va;
         else tva = C.tail_va32;
@@ -1138,7 +1190,10 @@ DotRef amg_hierarchy::kcycle(int k, const T *rr, T *xx, const T *wdot, const RtS
             mode = 2;
         }
     }
-    if (k == 0) kd0 = kd;
+    if (k == 0) {
+        kd0 = kd;
+        mode0 = mode;
+    }
     return launch_post_smooth<T>(F.A, F.ci, FK.va, FK.minv, rr, F.agg_pos, F.cagg, mode, edirect, CK.c1, CK.c2, kd, xx,
                                  wdot, k == 0 ? d_zq : DotBuf{}, flag, F.G, stream, ainv, C.n, ncol, F.xs, F.sl(),
                                  FK.sva, gate, second);
@@ -1357,11 +1412,11 @@ void amg_hierarchy::autotune(int ncol)
 void amg_hierarchy::capture_graphs(int ncol)
 {
     // The K-cycle visits level k 2^k times, so its graph has about 6 (2^L - 1)
-    // nodes; deep hierarchies (small aggregates) are launched eagerly instead.
+    // nodes (L the top of the one-workgroup levels where there are such); deep hierarchies (small aggregates) are launched eagerly instead.
     if (!opt.use_graph || graphs.count(ncol)) return;
     Graphs &G = graphs[ncol];
     const int L = levels() - 1;
-    if (L > kMaxGraphDepth) return;
+    if ((sub_top ? sub_top : L) > kMaxGraphDepth) return;
     // out NULL: record the body's launches and drop them (nothing runs)
     auto capture = [&](auto &&body, hipGraphExec_t *out) {
         hipGraph_t g = nullptr;
@@ -1822,17 +1877,17 @@ amg_status amg_time_smoother(amg_hierarchy *h, int32_t reps, double *avg_us, dou
 {
     if (!h || reps < 1 || !avg_us) return AMG_ERR_INVALID_ARGUMENT;
     if (h->levels() < 3) return AMG_ERR_UNSUPPORTED;
-    if (!h->kd0.rho1.part) return AMG_ERR_UNSUPPORTED;  // the step reads the products of a K-cycle already run
+    if (h->mode0 < 0) return AMG_ERR_UNSUPPORTED;  // the step reads the products of a K-cycle already run
     return guarded([&]() {
         const Level &F = h->lev[0], &C = h->lev[1];
-        const int mode = h->opt.kcycle_inner == 1 ? 1 : 2;
+        const int mode = h->mode0;
         auto launch = [&]() {  // as in the solve: the FP64 step also forms (z, q)
             if (h->mixed) {
                 amg::launch_post_smooth<float>(F.A, F.ci, F.k32.va, F.k32.minv, h->r32, F.agg_pos, F.cagg, mode,
-                                               nullptr, C.k32.c1, C.k32.c2, h->kd0, h->z32, nullptr, DotBuf{}, h->flag,
+                                               C.k32.c1, C.k32.c1, C.k32.c2, h->kd0, h->z32, nullptr, DotBuf{}, h->flag,
                                                F.G, h->stream, h->ainv, C.n, 1, F.xs, F.sl(), F.k32.sva);
             } else {
-                amg::launch_post_smooth<double>(F.A, F.ci, F.va, F.minv, h->r, F.agg_pos, F.cagg, mode, nullptr, C.c1,
+                amg::launch_post_smooth<double>(F.A, F.ci, F.va, F.minv, h->r, F.agg_pos, F.cagg, mode, C.c1, C.c1,
                                                 C.c2, h->kd0, h->z, h->q, h->d_zq, h->flag, F.G, h->stream, h->ainv,
                                                 C.n, 1, F.xs, F.sl(), F.k64.sva);
             }
