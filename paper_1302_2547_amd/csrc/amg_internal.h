@@ -236,47 +236,43 @@ template <class T>
 void launch_post_direct(Rows R, const int *ci, const T *va, const T *minv, const T *r, const T *v1, KDots kd,
                         DotRef om_r, DotRef om_v1, const double *ainv, T *xout, T *rt_out, int *flag, int G,
                         bool rt_mode, hipStream_t s, int ncol = 1, const int *gate = nullptr);
-// A small level whose coarse level is one unknown, laid out for a whole coarse
-// correction (two flexible-CG steps, Sec. 4.4) in one block of kTailThreads
-// threads per right-hand side.  Thread t owns rows t + u kTailThreads
-// (u < kTailRows); the entries of an owned ordinary row (at most kTailWidth) sit
-// in that thread's slots u kTailWidth .. u kTailWidth + kTailWidth - 1 in CSR
-// order, padded with zero values; the entries of at most kTailLong long rows
-// (the hub of the single aggregate has every row of the level as a neighbour)
-// fill the slots from kTailRows kTailWidth on: entry j of long row m sits in slot
-// kTailRows kTailWidth + long_slot[m] + j / kTailThreads of thread
-// j % kTailThreads.  ci[s kTailThreads + t] is slot s of thread t (the values are
-// a separate array of the same shape, per storage type); padding slots hold
-// column 0 and value 0.
-constexpr int kTailThreads = 1024;
-constexpr int kTailRows = 5;
-constexpr int kTailWidth = 2;
-constexpr int kTailLong = 2;
-constexpr int kTailLongSlots = 6;
-constexpr int kTailSlots = kTailRows * kTailWidth + kTailLongSlots;
-struct TailLayout {
-    int n;
-    int nlong;
-    int long_row[kTailLong];       // -1 when unused
-    int long_slot[kTailLong + 1];  // long row m: slots long_slot[m] .. long_slot[m+1] (after the row slots)
-    const uint16_t *ci;  // column indices (n <= kTailRows kTailThreads < 2^16)
+// A level whose coarse level is one unknown is a star: its single aggregate is a hub
+// and all of its neighbours, so every other row (leaf) holds its diagonal d and the
+// hub's column u, and a few rows also an entry of another leaf.  Such a level of at most
+// kStarMaxRows rows takes its whole coarse correction in one block of kStarThreads
+// threads per right-hand side (k_star_visit).  The rows with leaf-leaf entries (at most
+// kStarExtra per thread -- thread i % kStarThreads owns row i -- and kStarExtraRows in
+// all, which also are the places of their values in the exchange array) are listed per
+// thread, their entries (at most kStarExtraEntries) row by row.
+constexpr int kStarThreads = 1024;
+constexpr int kStarMaxRows = 8 * kStarThreads;
+constexpr int kStarExtra = 2, kStarExtraRows = 64, kStarExtraEntries = 256;
+struct StarInfo {
+    int ok, hub, extra;  // extra: leaf-leaf entries
 };
-// Builds the layout of a CSR level on the host; false when the level does not fit.
-bool build_tail_layout(int n, const int *rp, const int *ci, const double *va, std::vector<uint16_t> &tci,
-                       std::vector<double> &tva, TailLayout &L);
-// Both flexible-CG steps of a K-cycle visit of such a level from its restricted
-// residual rc: c1 = K(rc), v1 = A c1, rt = rc - (alpha1/rho1) v1, c2 = K(rt), where K
-// is the two-grid visit of k_post_direct (pre-smoothing, restriction by om,
-// coarse solve, prolongation, post-smoothing).  Writes c1 and c2 and the five
-// products as reduced values: d1[0] = rho1 = (c1, A c1), d1[1] = alpha1 = (c1, rc),
-// d2[0] = beta = (c2, A c2), d2[1] = gamma = (c2, v1), d2[2] = alpha2 = (c2, rt).
-// theta2 > 0 (the squared K-cycle threshold): when (rt, rt) < theta2 (rc, rc) the
-// second step is skipped (c2 = 0, d2 = 0, so the caller's coefficients reduce to
-// the first step's).
+struct StarExtra {
+    int at[kStarExtra * kStarThreads];     // e * kStarThreads + t: slot i / kStarThreads | place << 8, or -1
+    int range[kStarExtra * kStarThreads];  // that row's entries: first | end << 16
+    int col[kStarExtraEntries];            // place of the column
+    double val[kStarExtraEntries];
+};
+struct StarLayout {
+    int n = 0, hub = 0, extra = 0;
+    const void *d = nullptr, *u = nullptr;  // type T, per row (u of the hub: 0)
+    const StarExtra *ext = nullptr;
+};
+// Fills d, u and the lists for a level of n rows (solve layout, values of type T) and
+// tells whether it is such a star.
 template <class T>
-void launch_tail_visit(const TailLayout &L, const T *va, const T *minv, const double *om, const double *ainv,
-                       const T *rc, T *c1, T *c2, double *d1, double *d2, int *flag, hipStream_t s, int ncol = 1,
-                       const int *gate = nullptr, double theta2 = 0.0);
+void launch_star_layout(int n, const int *rp, const int *ci, const T *va, T *d, T *u, StarExtra *ext, StarInfo *info,
+                        hipStream_t s);
+// e = the level's coarse correction for the restricted residual rc: nu flexible-CG steps
+// (Sec. 4.4), each preconditioned by the two-grid visit of k_post_direct
+// (pre-smoothing, exact solve of the single unknown, prolongation, post-smoothing).
+// theta2 > 0: the squared K-cycle threshold.
+template <class T>
+void launch_star_visit(const StarLayout &L, const T *minv, const double *ainv, const T *rc, T *e, int nu, int *flag,
+                       hipStream_t s, int ncol = 1, const int *gate = nullptr, double theta2 = 0.0);
 // rt = rc - (alpha1/rho1) v1
 template <class T>
 void launch_inner_residual(int n, const T *rc, const T *v1, KDots kd, T *rt, int *flag, hipStream_t s, int ncol = 1,

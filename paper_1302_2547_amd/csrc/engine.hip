@@ -279,10 +279,8 @@ struct Level {
     double *omega = nullptr;
     DotBuf d_om{};
     DotRef om_rc{}, om_v1{};
-    // ... and small enough for the one-block coarse correction (tail.n = 0: not laid out)
-    TailLayout tail{};
-    double *tail_va = nullptr;
-    float *tail_va32 = nullptr;
+    // ... or, where it is a star, its whole coarse correction is one block's (star.n = 0: it is not)
+    StarLayout star{};
     KArrays<double> k64{};
     KArrays<float> k32{};
     template <class T>
@@ -470,6 +468,7 @@ struct amg_hierarchy {
     void finalize_layout();
     void build_sell(int l, const int *rp, const int *ci, const double *va);
     void build_subtree();
+    void build_single_unknown();
     // the inner residual rt = rcf - (alpha1/rho1) v1 of a parent's first step
     template <class T>
     struct RtSource {
@@ -907,39 +906,6 @@ void amg_hierarchy::finalize_layout()
             }
         }
     }
-    // single coarse unknown below level L-1 (L >= 2): the restriction is the row
-    // vector om (launch_single_unknown_weights)
-    if (L >= 2 && lev[L].n == 1 && lev[L - 1].nnz <= (1 << 24)) {
-        Level &F = lev[L - 1];
-        F.omega = pool.alloc<double>(F.n);
-        launch_single_unknown_weights(F.n, F.rp, F.ci, F.va, F.minv, F.omega, stream);
-        F.d_om = dot_buf();
-        // the one-block coarse correction's layout is built on the host from the
-        // level's pattern (placement only, no arithmetic)
-        std::vector<int> rp(F.n + 1), ci(F.nnz);
-        std::vector<double> va(F.nnz);
-        to_host(rp.data(), F.rp, F.n + 1);
-        to_host(ci.data(), F.ci, F.nnz);
-        to_host(va.data(), F.va, F.nnz);
-        AMG_TRACE_MSG("level %d: single coarse unknown below, restriction by inner products", L - 1);
-        std::vector<uint16_t> tci;
-        std::vector<double> tva;
-        TailLayout tl{};
-        if (opt.kcycle_inner == 2 && build_tail_layout(F.n, rp.data(), ci.data(), va.data(), tci, tva, tl)) {
-            uint16_t *dci = pool.alloc<uint16_t>(tci.size());
-            to_dev(dci, tci.data(), tci.size());
-            F.tail_va = pool.alloc<double>(tva.size());
-            to_dev(F.tail_va, tva.data(), tva.size());
-            if (mixed) {
-                const std::vector<float> t32(tva.begin(), tva.end());
-                F.tail_va32 = pool.alloc<float>(t32.size());
-                to_dev(F.tail_va32, t32.data(), t32.size());
-            }
-            tl.ci = dci;
-            F.tail = tl;
-            AMG_TRACE_MSG("level %d: one-block coarse correction (%d long rows)", L - 1, tl.nlong);
-        }
-    }
     for (int l = 0; l <= L; l++) {
         Level &F = lev[l];
         F.k64 = KArrays<double>{F.va, F.minv, F.wv, F.rc, F.rt, F.c1, F.c2, F.v1, F.sell_va};
@@ -970,6 +936,7 @@ void amg_hierarchy::finalize_layout()
         z32 = pool.alloc<float>((size_t)lev[0].n * nr);
     }
     build_subtree();
+    build_single_unknown();
     const int n = lev[0].n;
     b = pool.alloc<double>((size_t)n * nr);
     x = pool.alloc<double>((size_t)n * nr);
@@ -1032,6 +999,42 @@ void amg_hierarchy::build_subtree()
                   sub.lds_bytes);
     for (int d = 1; d < count; d++)
         AMG_TRACE_MSG("level %d: %d rows in %d wavefront slots, %d long", L - d, n[d], need[d].waves, need[d].nover);
+}
+
+// A single coarse unknown below level L-1 (L >= 2, not in the subtree): the level is
+// a star, whose coarse correction one block forms where it is small enough; else the
+// restriction is the row vector om (launch_single_unknown_weights).
+void amg_hierarchy::build_single_unknown()
+{
+    using namespace amg;
+    const int L = levels() - 1;
+    if (L < 2 || sub_top || lev[L].n != 1 || lev[L - 1].nnz > (1 << 24)) return;
+    Level &F = lev[L - 1];
+    const size_t value = mixed ? sizeof(float) : sizeof(double);
+    const size_t rows = ((size_t)F.n * value + 15) / 16 * 16;
+    const size_t bytes = 2 * rows + sizeof(StarExtra) + sizeof(StarInfo);
+    if (F.n >= 3 && F.n <= kStarMaxRows && !(pool.budget && pool.used + bytes > pool.budget)) {
+        char *at = pool.alloc<char>(bytes);
+        StarExtra *ext = reinterpret_cast<StarExtra *>(at + 2 * rows);
+        StarInfo *dinfo = reinterpret_cast<StarInfo *>(ext + 1), info{};
+        if (mixed)
+            launch_star_layout<float>(F.n, F.rp, F.ci, F.k32.va, reinterpret_cast<float *>(at),
+                                      reinterpret_cast<float *>(at + rows), ext, dinfo, stream);
+        else
+            launch_star_layout<double>(F.n, F.rp, F.ci, F.va, reinterpret_cast<double *>(at),
+                                       reinterpret_cast<double *>(at + rows), ext, dinfo, stream);
+        to_host(&info, dinfo, 1);
+        if (info.ok) {
+            F.star = StarLayout{F.n, info.hub, info.extra, at, at + rows, ext};
+            AMG_TRACE_MSG("level %d: star of %d rows, %d entries between leaves, in one block", L - 1, F.n, info.extra);
+            return;
+        }
+        pool.release(at);
+    }
+    F.omega = pool.alloc<double>(F.n);
+    launch_single_unknown_weights(F.n, F.rp, F.ci, F.va, F.minv, F.omega, stream);
+    F.d_om = dot_buf();
+    AMG_TRACE_MSG("level %d: single coarse unknown below, restriction by inner products", L - 1);
 }
 
 // Sliced ELLPACK copies of the levels of at least kSmallLevel rows (not the last
@@ -1111,11 +1114,9 @@ DotRef amg_hierarchy::kcycle(int k, const T *rr, T *xx, const T *wdot, const RtS
     // only while ||rt|| >= theta ||rc||, decided on the device (the launches stay
     // the same, so the cycle is still one static graph)
     const double theta = opt.kcycle_threshold;
-    // C small with a single unknown below: the whole coarse correction in one block,
-    // which forms (om, rc) itself
-    const bool tail = C.tail.n > 0;
-    const bool subtree = sub_top > 0 && k + 1 == sub_top;  // C and all below it in one launch
-    const double *om = tail || subtree ? nullptr : C.omega;
+    // C and all below it in one launch, or C a star
+    const bool subtree = sub_top > 0 && k + 1 == sub_top, star = C.star.n > 0;
+    const double *om = C.omega;
     if (rts) {  // rr = rt is formed here from the parent's first inner step (never with a threshold)
         C.om_rc = launch_restrict_rt<T>(F.S, F.n, F.sci, FK.wv, rts->rcf, rts->v1, rts->kd, const_cast<T *>(rr),
                                         CK.rc, flag, F.Gs, stream, om, C.d_om, ncol, gate);
@@ -1134,15 +1135,11 @@ DotRef amg_hierarchy::kcycle(int k, const T *rr, T *xx, const T *wdot, const RtS
         launch_subtree<T>(sub, CK.rc, CK.c1, flag, stream, ncol, gate, theta * theta);
         mode = 0;
         edirect = CK.c1;
-    } else if (tail) {
-        const T *tva;
-        if constexpr (std::is_same<T, double>::value) tva = C.tail_va;
-        else tva = C.tail_va32;
-        double *d1 = C.d_c1.final_out, *d2 = C.d_c2.final_out;
-        launch_tail_visit<T>(C.tail, tva, CK.minv, C.omega, ainv, CK.rc, CK.c1, CK.c2, d1, d2, flag, stream, ncol,
-                             gate, theta * theta);
-        kd = KDots{DotRef{d1, 1}, DotRef{d1 + 1, 1}, DotRef{d2, 1}, DotRef{d2 + 1, 1}, DotRef{d2 + 2, 1}};
-        mode = 2;
+    } else if (star) {
+        launch_star_visit<T>(C.star, CK.minv, ainv, CK.rc, CK.c1, opt.kcycle_inner, flag, stream, ncol, gate,
+                             theta * theta);
+        mode = 0;
+        edirect = CK.c1;
     } else if (k + 1 == L) {
         if (C.n <= kInlineCoarse) {
             mode = 3;

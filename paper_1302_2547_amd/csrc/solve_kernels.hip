@@ -19,6 +19,7 @@
 // partial sets are reduced by every consumer block itself; large ones by one
 // extra block (k_reduce_partials).  Results are identical run to run and never
 // leave the device, so the K-cycle has no host round trip.
+#include "amg.h"
 #include "amg_internal.h"
 #include "wave_ops.h"
 
@@ -1319,239 +1320,296 @@ __global__ void __launch_bounds__(kBlock) k_post_direct(Rows R, const int *__res
         });
 }
 
-// ------------------------------------------------------------------ small single-aggregate level
+// ------------------------------------------------------------------ star level
 
-// Sum over a block of kTailThreads threads (16 wavefronts); every thread
-// receives the sums.
+// Sums of 4 N values over the block, the same in every thread (fixed order).  set: 0 or
+// 1, another one than that of the sums before (one barrier per call).
 template <int N>
-__device__ inline void tail_sums(double (&v)[N])
+__device__ __forceinline__ void star_sums(double (&v)[4 * N], int set)
 {
-    static_assert(kTailThreads / kWave == 16, "one wavefront sum per lane of a row of 16");
-    __shared__ double sh[N][kTailThreads / kWave];
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    static_assert(kStarThreads / kWave == 16, "the partials of a group of four fill a wavefront");
+    __shared__ double part[2][2][4 * (kStarThreads / kWave)];
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
 #pragma unroll
-    for (int d = 0; d < N; d++) {
-        const double t = wave_sum(v[d]);
-        if (lane == 0) sh[d][wid] = t;
+    for (int g = 0; g < N; g++) {
+        const double q[4] = {v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+        const double t = spread4_sum(q);
+        if (lane < 4) part[set][g][4 * w + lane] = t;
     }
     __syncthreads();
 #pragma unroll
-    for (int d = 0; d < N; d++) v[d] = lane_value(row16_sum(sh[d][lane & 15]), 0);
-    __syncthreads();
+    for (int g = 0; g < N; g++) {
+        const double t = mod4_sum(part[set][g][lane]);
+#pragma unroll
+        for (int d = 0; d < 4; d++) v[4 * g + d] = lane_value(t, d);
+    }
 }
 
-// The whole coarse correction of a K-cycle visit whose coarse level C is small
-// and has a single unknown below it: both flexible-CG steps (Sec. 4.4) on C, each
-// preconditioned by the two-grid visit of k_post_direct, in one block per
-// right-hand side.  C's entries stay in registers for the four products with A,
-// the vector being multiplied is shared through LDS (as are rc and M^-1 of the
-// owned rows), and every inner product is a block sum, so the correction takes
-// one launch instead of four.  Vectors that the separate kernels store in T are
-// rounded to T here at the same points (c1, A c1, rt, c2).
-template <class T, bool GATE, bool THETA>
-__global__ void __launch_bounds__(kTailThreads) k_tail_visit(TailLayout L, const T *__restrict__ va,
-                                                             const T *__restrict__ minv,
-                                                             const double *__restrict__ om,
+// The whole coarse correction of a star level (see StarLayout) in one block per
+// right-hand side.  A row of A touches its diagonal and the hub only, so a product
+// with A needs no gathers: a leaf's part is elementwise in registers, the hub's row is
+// an inner product.  The hub's values of a visit follow from sums of its input alone --
+// with x = M^-1 r + e, (A x)_hub = a_hh x_hub + sum u m r + e sum u -- so each
+// flexible-CG step is one elementwise pass and one block-wide sum (three sums in all;
+// the sums of the second step's input follow from the first step's by
+// rt = r - q y).  Every row costs four loads (r, M^-1, d, u); what bounds the kernel is
+// one compute unit's fetch of them.
+// R: rows per thread; EXTRA: there are leaf-leaf entries, whose columns are exchanged
+// through LDS for each of the four products.
+template <class T, int R, bool EXTRA>
+__global__ void __launch_bounds__(kStarThreads) k_star_visit(StarLayout L, const T *__restrict__ minv,
                                                              const double *__restrict__ ainv,
-                                                             const T *__restrict__ rc, T *__restrict__ c1,
-                                                             T *__restrict__ c2, double *__restrict__ d1,
-                                                             double *__restrict__ d2, int *__restrict__ flag,
-                                                             const int *__restrict__ gate, double theta2)
+                                                             const T *__restrict__ rc, T *__restrict__ eout, int nu,
+                                                             int *__restrict__ flag, const int *__restrict__ gate,
+                                                             double theta2)
 {
-    if (gated_off_if<GATE>(gate)) return;
-    constexpr int R = kTailRows, W = kTailWidth, S = kTailSlots, NL = kTailLong;
-    __shared__ double xs[R * kTailThreads];  // the vector being multiplied
-    __shared__ double rs[R * kTailThreads];  // rc (first step), then rt (second step)
-    __shared__ double ms[R * kTailThreads];  // M^-1
-    const int n = L.n, t = threadIdx.x;
+    if (gated_off(gate)) return;
+    const int n = L.n, t = threadIdx.x, hub = L.hub;
     rc = colv(rc, n);
-    c1 = colv(c1, n);
-    c2 = colv(c2, n);
-    d1 = colp(d1);
-    d2 = colp(d2);
-    // The owned rows' rc, M^-1 and om are loaded first (clamped indices, no
-    // branches) and the entries after them, so that the first block sum, which
-    // needs only the former, overlaps the arrival of the entries.
-    double o[R], rv[R], mv[R];
+    eout = colv(eout, n);
+    const T *dd = static_cast<const T *>(L.d), *uu = static_cast<const T *>(L.u);
+    // with many rows per thread, M^-1 and d wait in LDS for the registers' sake
+    constexpr bool kSpill = R > 5;
+    __shared__ double wait[kSpill ? 2 * R * kStarThreads : 1];
+    double r[R], u[R], mr[kSpill ? 1 : R], dr[kSpill ? 1 : R];
+    auto m = [&](int k) -> double & { return kSpill ? wait[2 * k * kStarThreads + t] : mr[kSpill ? 0 : k]; };
+    auto d = [&](int k) -> double & { return kSpill ? wait[(2 * k + 1) * kStarThreads + t] : dr[kSpill ? 0 : k]; };
 #pragma unroll
-    for (int u = 0; u < R; u++) {
-        const int i = t + u * kTailThreads < n ? t + u * kTailThreads : n - 1;
-        rv[u] = (double)rc[i];
-        mv[u] = (double)minv[i];
-        o[u] = om[i];
+    for (int k = 0; k < R; k++) {
+        const int i = t + k * kStarThreads < n ? t + k * kStarThreads : n - 1;
+        r[k] = (double)rc[i];
+        m(k) = (double)minv[i];
+        d(k) = (double)dd[i];
+        u[k] = (double)uu[i];
     }
-    int ci[S];
-    double a[S];
-#pragma unroll
-    for (int s = 0; s < S; s++) {
-        ci[s] = L.ci[s * kTailThreads + t];
-        a[s] = (double)va[s * kTailThreads + t];
-    }
-    // first row index of this wavefront's lanes (row slots of u are all padding
-    // for the whole wavefront when u * kTailThreads + wbase >= n)
-    const int wbase = __builtin_amdgcn_readfirstlane(t & ~(kWave - 1));
-    double q[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-    for (int u = 0; u < R; u++) {
-        const int i = t + u * kTailThreads;
-        if (i >= n) rv[u] = mv[u] = o[u] = 0.0;
-        rs[i] = rv[u];
-        ms[i] = mv[u];
-        q[0] += o[u] * rv[u];
-        if (THETA) q[1] += rv[u] * rv[u];  // (rc, rc) for the threshold test
-    }
-    const double acinv = ainv[0];
-    // y = (A xs) at the owned rows; the sums of long rows are block sums (whose
-    // barriers also end every thread's reads of xs)
-    auto apply = [&](double (&y)[R]) {
-        double p[S];
-#pragma unroll
-        for (int u = 0; u < R; u++) {
-            if (u * kTailThreads + wbase < n) {
-#pragma unroll
-                for (int k = 0; k < W; k++) p[u * W + k] = a[u * W + k] * xs[ci[u * W + k]];
-            } else {
-#pragma unroll
-                for (int k = 0; k < W; k++) p[u * W + k] = 0.0;
-            }
+    const double rh0 = (double)rc[hub], mh = (double)minv[hub], dh = (double)dd[hub], acinv = ainv[0];
+    constexpr int E = EXTRA ? kStarExtra : 0;
+    __shared__ double lval[EXTRA ? kStarExtraEntries : 1];
+    __shared__ int lcol[EXTRA ? kStarExtraEntries : 1];
+    int ext[E + 1], range[E + 1];
+    double exv[E + 1];  // sum of the listed row's entries
+    if (EXTRA) {
+        if (t < L.extra) {
+            lval[t] = L.ext->val[t];
+            lcol[t] = L.ext->col[t];
         }
 #pragma unroll
-        for (int s = R * W; s < S; s++) p[s] = a[s] * xs[ci[s]];
-#pragma unroll
-        for (int u = 0; u < R; u++) {
-            double acc = p[u * W];
-#pragma unroll
-            for (int k = 1; k < W; k++) acc += p[u * W + k];
-            y[u] = acc;
+        for (int e = 0; e < E; e++) {
+            ext[e] = L.ext->at[e * kStarThreads + t];
+            range[e] = L.ext->range[e * kStarThreads + t];
         }
-        double l[NL];
+        __syncthreads();
 #pragma unroll
-        for (int m = 0; m < NL; m++) {
-            l[m] = 0.0;
-            if (m < L.nlong) {
-#pragma unroll
-                for (int s = R * W; s < S; s++) {
-                    const int j = s - R * W;
-                    l[m] += (j >= L.long_slot[m] && j < L.long_slot[m + 1]) ? p[s] : 0.0;
-                }
-            }
+        for (int e = 0; e < E; e++) {
+            exv[e] = 0.0;
+            for (int p = range[e] & 0xffff; p < range[e] >> 16; p++) exv[e] += lval[p];
         }
-        tail_sums<NL>(l);
+    }
+    // the hub's slot and those past the last row count nothing in the leaves' sums
 #pragma unroll
-        for (int u = 0; u < R; u++) {
+    for (int k = 0; k < R; k++) {
+        const int i = t + k * kStarThreads;
+        if (i >= n || i == hub) r[k] = m(k) = d(k) = u[k] = 0.0;
+    }
+    // leaf-leaf parts of A v, to be added by slot
+    __shared__ double xs[EXTRA ? 2 : 1][EXTRA ? kStarExtraRows : 1];
+    double part[E + 1];
+    auto exchange = [&](const double (&v)[R], int set) {
+        if (!EXTRA) return;
 #pragma unroll
-            for (int m = 0; m < NL; m++)
-                if (t + u * kTailThreads == L.long_row[m]) y[u] = l[m];
+        for (int e = 0; e < E; e++) {
+#pragma unroll
+            for (int k = 0; k < R; k++)
+                if (ext[e] >= 0 && (ext[e] & 0xff) == k) xs[set][ext[e] >> 8] = v[k];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < E; e++) {
+            part[e] = 0.0;
+            for (int p = range[e] & 0xffff; p < range[e] >> 16; p++) part[e] += lval[p] * xs[set][lcol[p]];
         }
     };
-    // first step: c1 = K(rc) with e = (om, rc) / a_c
-    double om_r[1] = {q[0]}, rcrc = 0.0;
-    if (THETA) {
-        double v2[2] = {q[0], q[1]};
-        tail_sums<2>(v2);
-        om_r[0] = v2[0];
-        rcrc = v2[1];
-    } else {
-        tail_sums<1>(om_r);
-    }
-    const double e1 = acinv * om_r[0];
-    double x[R], y[R], c[R];
+    auto others = [&](int k, const double *p) {
+        double s = 0.0;
 #pragma unroll
-    for (int u = 0; u < R; u++) {
-        const int i = t + u * kTailThreads;
-        x[u] = ms[i] * rs[i] + e1;
-        xs[i] = x[u];
-    }
-    __syncthreads();
-    apply(y);
+        for (int e = 0; e < E; e++) s += ext[e] >= 0 && (ext[e] & 0xff) == k ? p[e] : 0.0;
+        return s;
+    };
+    // om_i = 1 - m_i (sum of column i): the restriction row vector
+    auto omega = [&](int k) { return 1.0 - m(k) * (d(k) + u[k] + others(k, exv)); };
+    double v1[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int u = 0; u < R; u++) {
-        const int i = t + u * kTailThreads;
-        const T cv = (T)(x[u] + ms[i] * (rs[i] - y[u]));
-        c[u] = (double)cv;
-        if (i < n) c1[i] = cv;
-        xs[i] = c[u];
+    for (int k = 0; k < R; k++) {
+        v1[0] += omega(k) * r[k];
+        v1[1] += u[k] * (m(k) * r[k]);
+        v1[2] += u[k];
+        v1[3] += r[k] * r[k];
     }
-    __syncthreads();
-    apply(y);  // A c1
-    double v[R];
-    q[0] = q[1] = q[2] = 0.0;
+    star_sums<1>(v1, 0);
+    const double usum = v1[2], omh = 1.0 - mh * (dh + usum), rcrc = v1[3] + rh0 * rh0;
+    double c[R], y[R];
+    // c = K(r) with e = acinv w and umr = sum u m r over the leaves; returns the hub's c
+    auto visit = [&](double rh, double w, double umr) {
+        const double e = acinv * w, xh = mh * rh + e;
 #pragma unroll
-    for (int u = 0; u < R; u++) {
-        const int i = t + u * kTailThreads;
-        v[u] = (double)(T)y[u];
-        if (i < n) {
-            q[0] += c[u] * y[u];
-            q[1] += c[u] * rs[i];
-            q[2] += o[u] * y[u];
-        }
+        for (int k = 0; k < R; k++) c[k] = m(k) * r[k] + e;
+        exchange(c, 0);
+#pragma unroll
+        for (int k = 0; k < R; k++)
+            c[k] += m(k) * (r[k] - (d(k) * c[k] + u[k] * xh + (EXTRA ? others(k, part) : 0.0)));
+        return xh + mh * (rh - (dh * xh + (umr + e * usum)));
+    };
+    const double w1 = v1[0] + omh * rh0, ch = visit(rh0, w1, v1[1]);
+    exchange(c, 1);
+    double v2[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < R; k++) {
+        y[k] = d(k) * c[k] + u[k] * ch + (EXTRA ? others(k, part) : 0.0);
+        v2[0] += u[k] * c[k];
+        v2[1] += c[k] * y[k];
+        v2[2] += c[k] * r[k];
+        v2[3] += omega(k) * y[k];
+        v2[4] += u[k] * (m(k) * y[k]);
     }
-    tail_sums<3>(q);
-    const double rho1 = q[0], alpha1 = q[1];
+    star_sums<2>(v2, 1);
+    const double yh = dh * ch + v2[0], rho1 = v2[1] + ch * yh, alpha1 = v2[2] + ch * rh0;
     // a zero coarse residual gives c1 = 0 and no correction; a non-positive rho1
     // otherwise means A is not SPD
-    const bool zero = rho1 == 0.0 && alpha1 == 0.0;
-    const bool bad = !(rho1 > 0.0) && !zero;
-    if (bad && t == 0) atomicOr(flag, 1);
-    const double al = (bad || zero) ? 0.0 : alpha1 / rho1;
-    // second step: rt = rc - (alpha1/rho1) v1, c2 = K(rt) with e = (om, rt) / a_c
-    const double e2 = acinv * (om_r[0] - al * q[2]);
-    double rtrt[1] = {0.0};
+    const bool ok = rho1 > 0.0;
+    if (!ok && !(rho1 == 0.0 && alpha1 == 0.0) && t == 0) atomicOr(flag, 1);
+    const double q = ok ? alpha1 / rho1 : 0.0;
+    auto store = [&](int k, double value, double hub_value) {
+        const int i = t + k * kStarThreads;
+        if (i < n) eout[i] = (T)(i == hub ? hub_value : value);
+    };
+    bool two = nu == 2;
+    const double rh = rh0 - q * yh;
+    if (two && theta2 > 0.0) {  // threshold test (Sec. 4.3): skip the second step
+        double v[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int u = 0; u < R; u++) {
-        const int i = t + u * kTailThreads;
-        const double rr = rs[i] - al * v[u];
-        x[u] = ms[i] * rr + e2;
-        rs[i] = rr;
-        xs[i] = x[u];
-        if (THETA && i < n) rtrt[0] += (double)(T)rr * (double)(T)rr;
+        for (int k = 0; k < R; k++) {
+            const double rt = r[k] - q * y[k];
+            v[0] += rt * rt;
+        }
+        star_sums<1>(v, 0);
+        if (v[0] + rh * rh < theta2 * rcrc) two = false;
+        __syncthreads();  // set 0 is written again below
     }
-    if (THETA) {  // threshold test (Sec. 4.3): skip the second step, c2 = 0
-        tail_sums<1>(rtrt);
-        if (rtrt[0] < theta2 * rcrc) {
+    if (!two) {
 #pragma unroll
-            for (int u = 0; u < R; u++) {
-                const int i = t + u * kTailThreads;
-                if (i < n) c2[i] = (T)0.0;
-            }
-            if (t == 0) {
-                d1[0] = rho1;
-                d1[1] = alpha1;
-                d2[0] = d2[1] = d2[2] = 0.0;
-            }
-            return;
+        for (int k = 0; k < R; k++) store(k, q * c[k], q * ch);
+        return;
+    }
+    double c1[R];
+#pragma unroll
+    for (int k = 0; k < R; k++) {
+        c1[k] = c[k];
+        r[k] -= q * y[k];
+    }
+    const double c2h = visit(rh, w1 - q * (v2[3] + omh * yh), v1[1] - q * v2[4]);
+    exchange(c, 1);
+    double v3[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < R; k++) {
+        const double y2 = d(k) * c[k] + u[k] * c2h + (EXTRA ? others(k, part) : 0.0);
+        v3[0] += u[k] * c[k];
+        v3[1] += c[k] * y2;
+        v3[2] += c[k] * y[k];
+        v3[3] += c[k] * r[k];
+    }
+    star_sums<1>(v3, 0);
+    const double beta = v3[1] + c2h * (dh * c2h + v3[0]), gamma = v3[2] + c2h * yh, alpha2 = v3[3] + c2h * rh;
+    double a1 = q, a2 = 0.0;
+    if (ok) {
+        const double g1 = gamma / rho1, rho2 = beta - gamma * g1;
+        if (rho2 > 0.0) {
+            a2 = alpha2 / rho2;
+            a1 = q - g1 * a2;
+        } else if (!(beta == 0.0 && alpha2 == 0.0) && t == 0) {
+            atomicOr(flag, 1);
         }
     }
-    __syncthreads();
-    apply(y);  // A x
 #pragma unroll
-    for (int u = 0; u < R; u++) {
-        const int i = t + u * kTailThreads;
-        const T cv = (T)(x[u] + ms[i] * (rs[i] - y[u]));
-        c[u] = (double)cv;
-        if (i < n) c2[i] = cv;
-        xs[i] = c[u];
-    }
-    __syncthreads();
-    apply(y);  // A c2
-    q[0] = q[1] = q[2] = 0.0;
-#pragma unroll
-    for (int u = 0; u < R; u++) {
-        const int i = t + u * kTailThreads;
-        if (i < n) {
-            q[0] += c[u] * y[u];
-            q[1] += c[u] * v[u];
-            q[2] += c[u] * (double)(T)rs[i];
-        }
-    }
-    tail_sums<3>(q);
+    for (int k = 0; k < R; k++) store(k, a1 * c1[k] + a2 * c[k], a1 * ch + a2 * c2h);
+}
+
+// One block: finds the hub (a row that holds every column) and lays the other rows out.
+template <class T>
+__global__ void __launch_bounds__(kStarThreads) k_star_layout(int n, const int *__restrict__ rp,
+                                                              const int *__restrict__ ci, const T *__restrict__ va,
+                                                              T *__restrict__ d, T *__restrict__ u,
+                                                              StarExtra *__restrict__ ext, StarInfo *__restrict__ info)
+{
+    __shared__ int hub, bad, rows, entries, row_of[kStarExtraRows], col_of[kStarExtraEntries];
+    const int t = threadIdx.x;
     if (t == 0) {
-        d1[0] = rho1;
-        d1[1] = alpha1;
-        d2[0] = q[0];
-        d2[1] = q[1];
-        d2[2] = q[2];
+        hub = n;
+        bad = rows = entries = 0;
     }
+    __syncthreads();
+    for (int i = t; i < n; i += kStarThreads)
+        if (rp[i + 1] - rp[i] == n) atomicMin(&hub, i);
+    __syncthreads();
+    const int h = hub;
+    if (h == n || n < 3) {
+        if (t == 0) *info = StarInfo{0, 0, 0};
+        return;
+    }
+    int count = 0;
+    bool wrong = false;
+    for (int i = t, k = 0; i < n; i += kStarThreads, k++) {
+        const int b = rp[i], e = rp[i + 1];
+        T di = T(0), ui = T(0);
+        int more = 0;  // leaf-leaf entries
+        for (int p = b; p < e; p++) {
+            const int j = ci[p];
+            if (j == i) di = va[p];
+            else if (i == h) continue;
+            else if (j == h) ui = va[p];
+            else more++;
+        }
+        d[i] = di;
+        u[i] = ui;
+        if (more == 0) continue;
+        if (count == kStarExtra || more > kStarExtraEntries) {
+            wrong = true;
+            break;
+        }
+        const int place = atomicAdd(&rows, 1), first = atomicAdd(&entries, more);
+        if (place >= kStarExtraRows || first + more > kStarExtraEntries) {
+            wrong = true;
+            break;
+        }
+        row_of[place] = i;
+        ext->at[count * kStarThreads + t] = k | place << 8;
+        ext->range[count * kStarThreads + t] = first | (first + more) << 16;
+        count++;
+        for (int p = b, q = first; p < e; p++) {
+            if (ci[p] == i || ci[p] == h) continue;
+            col_of[q] = ci[p];
+            ext->val[q++] = (double)va[p];
+        }
+    }
+    for (; count < kStarExtra; count++) {
+        ext->at[count * kStarThreads + t] = -1;
+        ext->range[count * kStarThreads + t] = 0;
+    }
+    if (wrong) bad = 1;
+    __syncthreads();
+    if (bad == 0) {  // (the same in every thread: no thread writes it before the next barrier)
+        bool lost = false;
+        for (int q = t; q < entries; q += kStarThreads) {
+            int place = -1;
+            for (int x = 0; x < rows; x++)
+                if (row_of[x] == col_of[q]) place = x;
+            lost = lost || place < 0;  // the column's own row lists no such entry
+            ext->col[q] = place < 0 ? 0 : place;
+        }
+        __syncthreads();
+        if (lost) bad = 1;
+    }
+    __syncthreads();
+    if (t == 0) *info = StarInfo{bad ? 0 : 1, h, entries};
 }
 
 // Y = A_c^-1 X on the coarsest level for CB right-hand sides per block (see
@@ -2150,58 +2208,29 @@ void launch_post_direct(Rows R, const int *ci, const T *va, const T *minv, const
 }
 
 template <class T>
-void launch_tail_visit(const TailLayout &L, const T *va, const T *minv, const double *om, const double *ainv,
-                       const T *rc, T *c1, T *c2, double *d1, double *d2, int *flag, hipStream_t s, int ncol,
-                       const int *gate, double theta2)
+void launch_star_layout(int n, const int *rp, const int *ci, const T *va, T *d, T *u, StarExtra *ext, StarInfo *info,
+                        hipStream_t s)
 {
-#define AMG_TAIL(GT, TH)                                                                                           \
-    k_tail_visit<T, GT, TH><<<dim3(1, ncol), kTailThreads, 0, s>>>(L, va, minv, om, ainv, rc, c1, c2, d1, d2, flag, gate, \
-                                                                   theta2)
-    if (gate) {
-        if (theta2 > 0.0) { AMG_TAIL(true, true); } else { AMG_TAIL(true, false); }
-    } else {
-        if (theta2 > 0.0) { AMG_TAIL(false, true); } else { AMG_TAIL(false, false); }
-    }
-#undef AMG_TAIL
+    if (n < 1 || n > kStarMaxRows) throw Error(AMG_ERR_DEVICE, "star level size");
+    k_star_layout<T><<<1, kStarThreads, 0, s>>>(n, rp, ci, va, d, u, ext, info);
     AMG_HIP(hipGetLastError());
 }
 
-bool build_tail_layout(int n, const int *rp, const int *ci, const double *va, std::vector<uint16_t> &tci,
-                       std::vector<double> &tva, TailLayout &L)
+template <class T>
+void launch_star_visit(const StarLayout &L, const T *minv, const double *ainv, const T *rc, T *e, int nu, int *flag,
+                       hipStream_t s, int ncol, const int *gate, double theta2)
 {
-    if (n < 1 || n > kTailRows * kTailThreads) return false;
-    L = TailLayout{};
-    L.n = n;
-    for (int m = 0; m < kTailLong; m++) L.long_row[m] = -1;
-    tci.assign((size_t)kTailSlots * kTailThreads, 0);  // padding: column 0, value 0
-    tva.assign((size_t)kTailSlots * kTailThreads, 0.0);
-    constexpr int first_long = kTailRows * kTailWidth;
-    int nlong = 0, used = 0;
-    for (int i = 0; i < n; i++) {
-        const int b = rp[i], len = rp[i + 1] - b;
-        if (len <= kTailWidth) {
-            const int t = i % kTailThreads, u = i / kTailThreads;
-            for (int k = 0; k < len; k++) {
-                const size_t at = (size_t)(u * kTailWidth + k) * kTailThreads + t;
-                tci[at] = (uint16_t)ci[b + k];
-                tva[at] = va[b + k];
-            }
-            continue;
-        }
-        const int slots = (len + kTailThreads - 1) / kTailThreads;
-        if (nlong == kTailLong || used + slots > kTailLongSlots) return false;
-        for (int j = 0; j < len; j++) {
-            const size_t at = (size_t)(first_long + used + j / kTailThreads) * kTailThreads + j % kTailThreads;
-            tci[at] = (uint16_t)ci[b + j];
-            tva[at] = va[b + j];
-        }
-        L.long_row[nlong] = i;
-        used += slots;
-        L.long_slot[++nlong] = used;
+    if (L.n < 1 || L.n > kStarMaxRows) throw Error(AMG_ERR_DEVICE, "star level size");
+#define AMG_STAR(R, X)                                                                                              \
+    k_star_visit<T, R, X><<<dim3(1, ncol), kStarThreads, 0, s>>>(L, minv, ainv, rc, e, nu, flag, gate, theta2)
+    const int rows = (L.n + kStarThreads - 1) / kStarThreads;
+    if (L.extra) {
+        if (rows <= 2) { AMG_STAR(2, true); } else if (rows <= 5) { AMG_STAR(5, true); } else { AMG_STAR(8, true); }
+    } else {
+        if (rows <= 2) { AMG_STAR(2, false); } else if (rows <= 5) { AMG_STAR(5, false); } else { AMG_STAR(8, false); }
     }
-    for (int m = nlong; m < kTailLong; m++) L.long_slot[m + 1] = used;  // empty ranges
-    L.nlong = nlong;
-    return true;
+#undef AMG_STAR
+    AMG_HIP(hipGetLastError());
 }
 
 template <class T>
@@ -2269,9 +2298,10 @@ void launch_to_float(int64_t n, const double *src, float *dst, hipStream_t s)
                                         DotRef, DotRef, const double *, T *, T *, int *, int, bool, hipStream_t,    \
                                         int, const int *);                                                          \
     template void launch_coarse_solve<T>(const CoarseSolve &, const T *, T *, hipStream_t, int);                   \
-    template void launch_tail_visit<T>(const TailLayout &, const T *, const T *, const double *, const double *,    \
-                                       const T *, T *, T *, double *, double *, int *, hipStream_t, int,            \
-                                       const int *, double);
+    template void launch_star_layout<T>(int, const int *, const int *, const T *, T *, T *, StarExtra *,            \
+                                        StarInfo *, hipStream_t);                                                   \
+    template void launch_star_visit<T>(const StarLayout &, const T *, const double *, const T *, T *, int, int *,   \
+                                       hipStream_t, int, const int *, double);
 AMG_INSTANTIATE(double)
 AMG_INSTANTIATE(float)
 #undef AMG_INSTANTIATE

@@ -25,41 +25,11 @@ struct SubCoef {
     bool two;
 };
 
-// Cross-lane moves that keep lane % 4: rotations inside rows of 16 lanes, then the
-// exchange of rows (gfx950's permlane swaps: with both operands equal they give the
-// even and the odd rows, the low and the high half).
-constexpr int kDppRowRor4 = 0x124, kDppRowRor8 = 0x128;
-__device__ __forceinline__ double rows_pair_sum(double v)  // over two neighbouring rows of 16
-{
-    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
-    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
-}
-__device__ __forceinline__ double halves_sum(double v)  // over the two halves of the wavefront
-{
-    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
-    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
-}
-// Sum over the lanes with the same lane % 4 (lanes 0 to 3 hold the result)
-__device__ __forceinline__ double mod4_sum(double v)
-{
-    v += dpp_f64<kDppRowRor4>(v);
-    v += dpp_f64<kDppRowRor8>(v);
-    return halves_sum(rows_pair_sum(v));
-}
-
-// Sums of four values over the block, in two parts around a barrier.  Each wavefront
-// first spreads the four values over the lanes (after two exchanges lane t holds one
-// of them, summed over its quad), so one chain of moves reduces all four: about a
-// third of the instructions of four separate sums.
+// Sums of four values over the block, in two parts around a barrier.
 __device__ __forceinline__ void sub_partials(const double (&v)[4], double *part)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    const bool b0 = lane & 1, b1 = lane & 2;
-    const double x = (b0 ? v[1] : v[0]) + dpp_f64<kDppQuadXor1>(b0 ? v[0] : v[1]);
-    const double y = (b0 ? v[3] : v[2]) + dpp_f64<kDppQuadXor1>(b0 ? v[2] : v[3]);
-    const double t = mod4_sum((b1 ? y : x) + dpp_f64<kDppQuadXor2>(b1 ? x : y));
+    const double t = spread4_sum(v);
     if (lane < 4) part[threadIdx.x / kWave * 4 + lane] = t;
 }
 // After the barrier: the totals, the same in every thread.

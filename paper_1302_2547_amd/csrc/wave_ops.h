@@ -60,5 +60,41 @@ __device__ inline double group_sum(double v)
     return v;
 }
 
+// Cross-lane moves that keep lane % 4: rotations inside rows of 16 lanes, then the
+// exchange of rows (gfx950's permlane swaps: with both operands equal they give the
+// even and the odd rows, the low and the high half).
+constexpr int kDppRowRor4 = 0x124, kDppRowRor8 = 0x128;
+__device__ __forceinline__ double rows_pair_sum(double v)  // over two neighbouring rows of 16
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+__device__ __forceinline__ double halves_sum(double v)  // over the two halves of the wavefront
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+// Sum over the lanes with the same lane % 4 (lanes 0 to 3 hold the result)
+__device__ __forceinline__ double mod4_sum(double v)
+{
+    v += dpp_f64<kDppRowRor4>(v);
+    v += dpp_f64<kDppRowRor8>(v);
+    return halves_sum(rows_pair_sum(v));
+}
+// Sums of four values over the wavefront: lane d (0 to 3) receives the d-th.  The four
+// values are first spread over the lanes (after two exchanges lane t holds one of them,
+// summed over its quad), so one chain of moves reduces all four: about a third of the
+// instructions of four separate sums.
+__device__ __forceinline__ double spread4_sum(const double (&v)[4])
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const bool b0 = lane & 1, b1 = lane & 2;
+    const double x = (b0 ? v[1] : v[0]) + dpp_f64<kDppQuadXor1>(b0 ? v[0] : v[1]);
+    const double y = (b0 ? v[3] : v[2]) + dpp_f64<kDppQuadXor1>(b0 ? v[2] : v[3]);
+    return mod4_sum((b1 ? y : x) + dpp_f64<kDppQuadXor2>(b1 ? x : y));
+}
+
 }  // namespace
 }  // namespace amg
