@@ -124,6 +124,12 @@ constexpr int kDoneStride = 32;  // one 128-byte line per slot
 void launch_mis_pass(int n, const int *rp, const int *ci, uint64_t *key, uint64_t *m1, int *owner, int cap, int G,
                      unsigned *done_counter, const int *hubs, int nhub, int lim, hipStream_t s);
 void launch_sum_slots(const unsigned *slots, unsigned *out, hipStream_t s);
+// The whole aggregation of a level that fits in one block's LDS: the aggregate of every
+// row, aptr (nc + 1), the members and tptr (nc + 1, exclusive sums of the aggregates'
+// row lengths); info[0] = passes (-1: no progress), info[1] = nc.
+bool aggregate_small_fits(int n, int nnz);
+void launch_aggregate_small(int n, int nnz, const int *rp, const int *ci, uint32_t s_l, int cap, int *agg, int *aptr,
+                            int *members, int *tptr, int *info, hipStream_t s);
 void launch_centre_flags(int n, const int *owner, int *flag, hipStream_t s);
 void launch_assign_aggregates(int n, const int *owner, const int *cid, int *agg, int *centre_of, hipStream_t s);
 void launch_member_counts(int nc, const int *rp, const int *ci, const int *owner, const int *centre_of, int *size,
@@ -144,9 +150,9 @@ bool trace_on();
 // Largest coarse level size whose dense accumulator fits in LDS beside the big-row
 // kernel's other shared arrays; rows of such levels need no global scratch.
 int coarse_acc_capacity();
-void launch_coarse_big_rows_acc(int nbig, const int *big_rows, int nc, const int *rp, const int *ci, const double *va,
-                                const int *agg, const int *aptr, const int *members, const int *tptr, int *tcol,
-                                double *tval, int *cnt, hipStream_t s);
+void launch_coarse_big_rows_acc(const unsigned *nbig, const int *big_rows, int nc, const int *rp, const int *ci,
+                                const double *va, const int *agg, const int *aptr, const int *members,
+                                const int *tptr, int *tcol, double *tval, int *cnt, hipStream_t s);
 void launch_coarse_big_rows(int nbig, const int *big_rows, const int64_t *scratch_off, uint64_t *skey,
                             const int *rp, const int *ci, const double *va, const int *agg, const int *aptr,
                             const int *members, const int *tptr, int *tcol, double *tval, int *cnt,

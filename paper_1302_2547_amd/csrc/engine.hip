@@ -551,61 +551,85 @@ void amg_hierarchy::build(const amg_csr &A)
         const int G = lanes_for((double)nnz / n, n);
         AMG_TRACE_MSG("level %d: n=%d nnz=%d G=%d aggregation", l, n, nnz, G);
         const uint32_t s_l = (uint32_t)splitmix64(opt.seed, (uint64_t)index);
-        launch_priorities(n, lev[l].rp_nat, s_l, key, owner, stream);
-        AMG_HIP(hipMemsetAsync(done, 0, sizeof(unsigned) * kDoneSlots * kDoneStride, stream));
-        // hub rows (longer than 8 G) of this level, served by whole blocks in the passes
-        const int lim = 8 * G;
-        launch_long_rows(n, lev[l].rp_nat, lim, tptr, nullptr, tptr + n, scan_tmp, stream);
-        const int nhub = read_int(tptr + n);
-        if (nhub > 0) launch_long_rows(n, lev[l].rp_nat, lim, tptr, big_rows, nullptr, scan_tmp, stream);
-        // Passes are launched kPassBatch at a time and the processed count after each
-        // is read back once per batch: a pass over a fully processed level changes
-        // nothing, so the passes past the last useful one are no-ops, and the count
-        // of useful passes is exact.
-        constexpr int kPassBatch = 4;
-        unsigned *after = reinterpret_cast<unsigned *>(ibuf + 8);
-        unsigned after_h[kPassBatch];
-        int passes = 0;
-        unsigned processed = 0;
-        while (processed < (unsigned)n) {
-            for (int b = 0; b < kPassBatch; b++) {
-                launch_mis_pass(n, lev[l].rp_nat, lev[l].ci_nat, key, m1, owner, opt.max_aggregate, G, done,
-                                big_rows, nhub, lim, stream);
-                launch_sum_slots(done, after + b, stream);
-            }
-            to_host(after_h, after, kPassBatch);
-            for (int b = 0; b < kPassBatch && processed < (unsigned)n; b++) {
-                passes++;
-                if (after_h[b] <= processed || after_h[b] > (unsigned)n)
-                    throw Error(AMG_ERR_DEVICE, "aggregation made no progress");
-                processed = after_h[b];
-            }
-        }
-        AMG_TRACE_MSG("level %d: %d aggregation passes", l, passes);
-        // Sec. 5.1: aggregates numbered by increasing coarse-vertex index
-        launch_centre_flags(n, owner, cid, stream);
-        scan(cid, cid, n, ibuf + 3, scan_tmp);
-        const int nc = read_int(ibuf + 3);
-        if ((double)nc > opt.stall_ratio * (double)n) return false;  // coarsening stalled
         Level &F = lev[l];
-        F.passes = passes;
-        F.agg_nat = pool.alloc<int>(n);
-        launch_assign_aggregates(n, owner, cid, F.agg_nat, centre_of, stream);
-        launch_member_counts(nc, F.rp_nat, F.ci_nat, owner, centre_of, size, pairs, stream);
-        F.aptr_nat = pool.alloc<int>(nc + 1);
-        scan(size, F.aptr_nat, nc, F.aptr_nat + nc, scan_tmp);
-        F.members_nat = pool.alloc<int>(n);
-        launch_member_fill(nc, F.rp_nat, F.ci_nat, owner, centre_of, F.aptr_nat, F.members_nat, stream);
-        scan(pairs, tptr, nc, tptr + nc, scan_tmp);
+        int passes = 0, nc = 0;
+        const bool fits = !pool.budget || pool.used + 3 * sizeof(int) * ((size_t)n + 1) <= pool.budget;
+        if (fits && aggregate_small_fits(n, nnz)) {  // in one launch
+            int *agg = pool.alloc<int>(n), *aptr = pool.alloc<int>(n + 1), *members = pool.alloc<int>(n);
+            launch_aggregate_small(n, nnz, F.rp_nat, F.ci_nat, s_l, opt.max_aggregate, agg, aptr, members, tptr, ibuf + 8,
+                                   stream);
+            int got[2];
+            to_host(got, ibuf + 8, 2);
+            passes = got[0];
+            nc = got[1];
+            if (passes < 0) throw Error(AMG_ERR_DEVICE, "aggregation made no progress");
+            if ((double)nc > opt.stall_ratio * (double)n) {  // coarsening stalled
+                for (void *ptr : std::initializer_list<void *>{agg, aptr, members}) pool.release(ptr);
+                return false;
+            }
+            F.passes = passes;
+            F.agg_nat = agg;
+            F.aptr_nat = aptr;
+            F.members_nat = members;
+        } else {
+            launch_priorities(n, lev[l].rp_nat, s_l, key, owner, stream);
+            AMG_HIP(hipMemsetAsync(done, 0, sizeof(unsigned) * kDoneSlots * kDoneStride, stream));
+            // hub rows (longer than 8 G) of this level, served by whole blocks in the passes
+            const int lim = 8 * G;
+            launch_long_rows(n, lev[l].rp_nat, lim, tptr, nullptr, tptr + n, scan_tmp, stream);
+            const int nhub = read_int(tptr + n);
+            if (nhub > 0) launch_long_rows(n, lev[l].rp_nat, lim, tptr, big_rows, nullptr, scan_tmp, stream);
+            // Passes are launched kPassBatch at a time and the processed count after each
+            // is read back once per batch: a pass over a fully processed level changes
+            // nothing, so the passes past the last useful one are no-ops, and the count
+            // of useful passes is exact.
+            constexpr int kPassBatch = 4;
+            unsigned *after = reinterpret_cast<unsigned *>(ibuf + 8);
+            unsigned after_h[kPassBatch];
+            unsigned processed = 0;
+            while (processed < (unsigned)n) {
+                for (int b = 0; b < kPassBatch; b++) {
+                    launch_mis_pass(n, lev[l].rp_nat, lev[l].ci_nat, key, m1, owner, opt.max_aggregate, G, done,
+                                    big_rows, nhub, lim, stream);
+                    launch_sum_slots(done, after + b, stream);
+                }
+                to_host(after_h, after, kPassBatch);
+                for (int b = 0; b < kPassBatch && processed < (unsigned)n; b++) {
+                    passes++;
+                    if (after_h[b] <= processed || after_h[b] > (unsigned)n)
+                        throw Error(AMG_ERR_DEVICE, "aggregation made no progress");
+                    processed = after_h[b];
+                }
+            }
+            AMG_TRACE_MSG("level %d: %d aggregation passes", l, passes);
+            // Sec. 5.1: aggregates numbered by increasing coarse-vertex index
+            launch_centre_flags(n, owner, cid, stream);
+            scan(cid, cid, n, ibuf + 3, scan_tmp);
+            nc = read_int(ibuf + 3);
+            if ((double)nc > opt.stall_ratio * (double)n) return false;  // coarsening stalled
+            F.passes = passes;
+            F.agg_nat = pool.alloc<int>(n);
+            launch_assign_aggregates(n, owner, cid, F.agg_nat, centre_of, stream);
+            launch_member_counts(nc, F.rp_nat, F.ci_nat, owner, centre_of, size, pairs, stream);
+            F.aptr_nat = pool.alloc<int>(nc + 1);
+            scan(size, F.aptr_nat, nc, F.aptr_nat + nc, scan_tmp);
+            F.members_nat = pool.alloc<int>(n);
+            launch_member_fill(nc, F.rp_nat, F.ci_nat, owner, centre_of, F.aptr_nat, F.members_nat, stream);
+            scan(pairs, tptr, nc, tptr + nc, scan_tmp);
+        }
         AMG_HIP(hipMemsetAsync(big_count, 0, sizeof(unsigned), stream));
         launch_coarse_rows(nc, F.rp_nat, F.ci_nat, F.va_nat, F.agg_nat, F.aptr_nat, F.members_nat, tptr, tcol, tval,
                            cnt, big_rows, big_count, stream);
-        const int nbig = read_int(reinterpret_cast<int *>(big_count));
-        AMG_TRACE_MSG("level %d: passes=%d nc=%d big rows=%d", l, passes, nc, nbig);
-        if (nbig > 0 && nc <= acc_cap) {  // dense accumulator in LDS, rows listed on the device
-            launch_coarse_big_rows_acc(nbig, big_rows, nc, F.rp_nat, F.ci_nat, F.va_nat, F.agg_nat, F.aptr_nat,
+        int nbig = 0;
+        if (nc <= acc_cap) {  // dense accumulator in LDS, rows listed (and counted) on the device
+            launch_coarse_big_rows_acc(big_count, big_rows, nc, F.rp_nat, F.ci_nat, F.va_nat, F.agg_nat, F.aptr_nat,
                                        F.members_nat, tptr, tcol, tval, cnt, stream);
-        } else if (nbig > 0) {
+            AMG_TRACE_MSG("level %d: passes=%d nc=%d", l, passes, nc);
+        } else {
+            nbig = read_int(reinterpret_cast<int *>(big_count));
+            AMG_TRACE_MSG("level %d: passes=%d nc=%d big rows=%d", l, passes, nc, nbig);
+        }
+        if (nbig > 0) {
             std::vector<int> rows(nbig), tp(nc + 1);
             to_host(rows.data(), big_rows, nbig);
             to_host(tp.data(), tptr, nc + 1);

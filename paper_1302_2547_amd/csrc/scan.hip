@@ -2,7 +2,7 @@
 // "generalised prefix sum" the paper uses to number aggregates, Sec. 5.1).
 //
 // Three launches: per-block totals, a single-block scan of the totals, and a
-// block-local scan plus the block's offset.  Integer sums are exact, so the result
+// block-local scan plus the block's offset (short arrays: one block, one launch).  Integer sums are exact, so the result
 // does not depend on the schedule.
 #include "amg_internal.h"
 
@@ -95,6 +95,48 @@ __global__ void __launch_bounds__(kBlock) k_scan_apply(const int *in, int *out, 
     }
 }
 
+// The whole scan by one block, for short arrays: one launch instead of three (each is a
+// few microseconds of a setup's latency; at 16,384 elements the block takes about as
+// long as they do).  in may alias out: a tile is read before it is written.
+constexpr int kOneBlock = 1024, kOneItems = 4;
+constexpr int64_t kOneBlockMax = 16384;
+__global__ void __launch_bounds__(kOneBlock) k_scan_one(const int *in, int *out, int n, int *__restrict__ total_dev)
+{
+    __shared__ int sh[2][kOneBlock / kWave];
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    int carry = 0, set = 0;
+    for (int base = 0; base < n; base += kOneBlock * kOneItems, set ^= 1) {
+        const int first = base + (int)threadIdx.x * kOneItems;
+        int v[kOneItems], s = 0;
+#pragma unroll
+        for (int k = 0; k < kOneItems; k++) {
+            v[k] = first + k < n ? in[first + k] : 0;
+            s += v[k];
+        }
+        int x = s;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int y = __shfl_up(x, o, kWave);
+            if (lane >= o) x += y;
+        }
+        if (lane == kWave - 1) sh[set][wid] = x;
+        __syncthreads();
+        int ex = carry + x - s;
+#pragma unroll
+        for (int w = 0; w < kOneBlock / kWave; w++) {
+            const int t = sh[set][w];
+            if (w < wid) ex += t;
+            carry += t;
+        }
+#pragma unroll
+        for (int k = 0; k < kOneItems; k++) {
+            if (first + k < n) out[first + k] = ex;
+            ex += v[k];
+        }
+    }
+    if (threadIdx.x == 0 && total_dev) *total_dev = carry;
+}
+
 }  // namespace
 
 size_t scan_tmp_ints(int64_t n) { return (size_t)((n + kTile - 1) / kTile) + 1; }
@@ -103,6 +145,11 @@ void scan_exclusive(const int *in, int *out, int64_t n, int *total_dev, int *tmp
 {
     if (n <= 0) {
         if (total_dev) AMG_HIP(hipMemsetAsync(total_dev, 0, sizeof(int), s));
+        return;
+    }
+    if (n <= kOneBlockMax) {
+        k_scan_one<<<1, kOneBlock, 0, s>>>(in, out, (int)n, total_dev);
+        AMG_HIP(hipGetLastError());
         return;
     }
     const int nb = (int)((n + kTile - 1) / kTile);

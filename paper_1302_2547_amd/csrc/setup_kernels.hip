@@ -447,6 +447,229 @@ __global__ void __launch_bounds__(kBlock) k_member_fill(int nc, const int *__res
     }
 }
 
+// ------------------------------------------------------------------ small levels
+
+// The whole aggregation of a small level in one block: priorities, the passes of
+// Alg. 2, the numbering of Sec. 5.1 and the member lists, with the pattern, the keys
+// and the maxima in LDS (16-bit indices).  A level of a thousand rows takes about ten
+// passes; launched one by one, with the count of processed vertices read back, they
+// and the scans around them cost 0.25-0.4 ms of latency for some 20 us of work.  The
+// decisions are those of k_mis_max1 / k_mis_select_claim: every pass reads the keys and
+// maxima of the one before, and the order in which rows are served does not matter.
+constexpr int kAggThreads = 1024, kAggLanes = 4, kAggLim = 64;
+
+struct SmallLayout {
+    size_t key, m1, owner, rp, ci, hubs, bytes;
+};
+__host__ __device__ inline SmallLayout small_layout(int n, int nnz)
+{
+    SmallLayout L;
+    L.key = 0;                                       // then the sizes and pair counts (int each)
+    L.m1 = 8 * (size_t)n;                            // then the coarse indices (int)
+    L.owner = L.m1 + 8 * (size_t)n;
+    L.rp = L.owner + 2 * (size_t)n;
+    L.ci = L.rp + 2 * ((size_t)n + 1);
+    L.hubs = L.ci + 2 * (size_t)nnz;
+    L.bytes = (L.hubs + 2 * ((size_t)nnz / kAggLim + 1) + 7) / 8 * 8;
+    return L;
+}
+
+// Exclusive prefix sums of a[0 .. n) in LDS, in place; returns the total.  Every thread
+// owns a contiguous piece.
+__device__ inline int lds_scan(int *a, int n, int *sh)
+{
+    const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
+    const int each = (n + kAggThreads - 1) / kAggThreads, b = min(t * each, n), e = min(b + each, n);
+    int s = 0;
+    for (int i = b; i < e; i++) s += a[i];
+    int x = s;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int y = __shfl_up(x, o, kWave);
+        if (lane >= o) x += y;
+    }
+    if (lane == kWave - 1) sh[w] = x;
+    __syncthreads();
+    int before = x - s, all = 0;
+    for (int k = 0; k < kAggThreads / kWave; k++) {
+        if (k < w) before += sh[k];
+        all += sh[k];
+    }
+    for (int i = b; i < e; i++) {
+        const int v = a[i];
+        a[i] = before;
+        before += v;
+    }
+    __syncthreads();
+    return all;
+}
+
+__global__ void __launch_bounds__(kAggThreads) k_aggregate_small(int n, int nnz, const int *__restrict__ rp_in,
+                                                                 const int *__restrict__ ci_in, uint32_t s_l, int cap,
+                                                                 int *__restrict__ agg_out, int *__restrict__ aptr_out,
+                                                                 int *__restrict__ members_out,
+                                                                 int *__restrict__ tptr_out, int *__restrict__ info)
+{
+    extern __shared__ __align__(16) char lds[];
+    __shared__ int sh[kAggThreads / kWave], nhub;
+    __shared__ unsigned done;
+    const SmallLayout L = small_layout(n, nnz);
+    uint64_t *key = reinterpret_cast<uint64_t *>(lds + L.key), *m1 = reinterpret_cast<uint64_t *>(lds + L.m1);
+    uint16_t *owner = reinterpret_cast<uint16_t *>(lds + L.owner), *rp = reinterpret_cast<uint16_t *>(lds + L.rp);
+    uint16_t *ci = reinterpret_cast<uint16_t *>(lds + L.ci), *hubs = reinterpret_cast<uint16_t *>(lds + L.hubs);
+    constexpr int G = kAggLanes;
+    const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave, sub = t % G, gbase = lane - sub;
+    const uint64_t gmask = ((1ull << G) - 1ull) << gbase;
+    if (t == 0) nhub = 0;
+    __syncthreads();
+    for (int e = t; e < nnz; e += kAggThreads) ci[e] = (uint16_t)ci_in[e];
+    for (int i = t; i < n; i += kAggThreads) {
+        const int b = rp_in[i], e = rp_in[i + 1];
+        rp[i] = (uint16_t)b;
+        if (i == n - 1) rp[n] = (uint16_t)e;
+        const uint64_t whole = 12u * (uint64_t)(e - b - 1) + (uint64_t)(i % 12) + 1u;  // as k_priorities
+        key[i] = (whole << 32) | (uint64_t)fmix32((uint32_t)i ^ s_l);
+        owner[i] = 0xffff;
+        if (e - b > kAggLim) hubs[atomicAdd(&nhub, 1)] = (uint16_t)i;
+    }
+    __syncthreads();
+    int passes = 0;
+    unsigned processed = 0;
+    for (;;) {
+        if (t == 0) done = 0;
+        for (int i = t / G; i < n; i += kAggThreads / G) {
+            const int b = rp[i], e = rp[i + 1];
+            if (e - b > kAggLim) continue;
+            uint64_t m = 0;
+            if (key[i] != 0) {
+                for (int p = b + sub; p < e; p += G) {
+                    const uint64_t kj = key[ci[p]];
+                    m = kj > m ? kj : m;
+                }
+            }
+            m = group_max<G>(m);
+            if (sub == 0) m1[i] = m;
+        }
+        for (int h = wave; h < nhub; h += kAggThreads / kWave) {
+            const int i = hubs[h];
+            uint64_t m = 0;
+            if (key[i] != 0) {
+                for (int p = rp[i] + lane; p < rp[i + 1]; p += kWave) {
+                    const uint64_t kj = key[ci[p]];
+                    m = kj > m ? kj : m;
+                }
+            }
+            m = group_max<kWave>(m);
+            if (lane == 0) m1[i] = m;
+        }
+        __syncthreads();
+        // key[i] may be zeroed by a neighbouring coarse vertex meanwhile: one lane reads
+        // it and the group decides on that one value
+        auto claim = [&](int i, uint64_t ki, int first, int step, uint64_t mask, auto max_of) {
+            const int b = rp[i], e = rp[i + 1];
+            uint64_t m = 0;
+            for (int p = b + first; p < e; p += step) {
+                const uint64_t v = m1[ci[p]];
+                m = v > m ? v : m;
+            }
+            if (max_of(m) != ki) return;
+            int taken = 1;
+            for (int p0 = b; p0 < e; p0 += step) {
+                if (cap > 0 && taken >= cap) break;
+                const int p = p0 + first;
+                int j = -1;
+                bool cand = false;
+                if (p < e) {
+                    j = ci[p];
+                    cand = j != i && key[j] != 0;
+                }
+                const uint64_t bal = __ballot(cand) & mask;
+                const int rank = __popcll(bal & ((1ull << lane) - 1ull));
+                if (cand && (cap == 0 || taken + rank < cap)) {
+                    owner[j] = (uint16_t)i;
+                    key[j] = 0;
+                }
+                const int c = __popcll(bal);
+                taken += (cap > 0 && taken + c > cap) ? (cap - taken) : c;
+            }
+            if (first == 0) {
+                owner[i] = (uint16_t)i;
+                key[i] = 0;
+                atomicAdd(&done, (unsigned)taken);
+            }
+        };
+        for (int i = t / G; i < n; i += kAggThreads / G) {
+            if (rp[i + 1] - rp[i] > kAggLim) continue;
+            uint64_t ki = sub == 0 ? key[i] : 0;
+            ki = __shfl(ki, gbase, kWave);
+            if (ki != 0) claim(i, ki, sub, G, gmask, [](uint64_t v) { return group_max<G>(v); });
+        }
+        for (int h = wave; h < nhub; h += kAggThreads / kWave) {
+            const int i = hubs[h];
+            uint64_t ki = lane == 0 ? key[i] : 0;
+            ki = __shfl(ki, 0, kWave);
+            if (ki != 0) claim(i, ki, lane, kWave, ~0ull, [](uint64_t v) { return group_max<kWave>(v); });
+        }
+        __syncthreads();
+        const unsigned d = done;
+        __syncthreads();
+        passes++;
+        processed += d;
+        if (d == 0 || processed >= (unsigned)n) break;  // every pass processes a vertex, or the level is in error
+    }
+    if (processed != (unsigned)n) {
+        if (t == 0) info[0] = -1;
+        return;
+    }
+    int *cid = reinterpret_cast<int *>(lds + L.m1);
+    int *size = reinterpret_cast<int *>(lds + L.key), *pairs = size + n;
+    for (int i = t; i < n; i += kAggThreads) {
+        cid[i] = owner[i] == i ? 1 : 0;
+        size[i] = pairs[i] = 0;
+    }
+    __syncthreads();
+    const int nc = lds_scan(cid, n, sh);
+    for (int i = t; i < n; i += kAggThreads) {
+        const int I = cid[owner[i]];
+        agg_out[i] = I;
+        atomicAdd(&size[I], 1);
+        atomicAdd(&pairs[I], rp[i + 1] - rp[i]);
+    }
+    __syncthreads();
+    lds_scan(size, nc, sh);
+    const int total = lds_scan(pairs, nc, sh);
+    for (int I = t; I < nc; I += kAggThreads) {
+        aptr_out[I] = size[I];
+        tptr_out[I] = pairs[I];
+    }
+    // members in ascending order: walking the coarse vertex' row lists them so
+    auto fill = [&](int c, int first, int step, uint64_t mask) {
+        int k = size[cid[c]];
+        for (int p0 = rp[c]; p0 < rp[c + 1]; p0 += step) {
+            const int p = p0 + first;
+            int j = -1;
+            bool mem = false;
+            if (p < rp[c + 1]) {
+                j = ci[p];
+                mem = owner[j] == c;
+            }
+            const uint64_t bal = __ballot(mem) & mask;
+            if (mem) members_out[k + __popcll(bal & ((1ull << lane) - 1ull))] = j;
+            k += __popcll(bal);
+        }
+    };
+    for (int i = t / G; i < n; i += kAggThreads / G)
+        if (owner[i] == i && rp[i + 1] - rp[i] <= kAggLim) fill(i, sub, G, gmask);
+    for (int h = wave; h < nhub; h += kAggThreads / kWave)
+        if (owner[hubs[h]] == hubs[h]) fill(hubs[h], lane, kWave, ~0ull);
+    if (t == 0) {
+        aptr_out[nc] = n;
+        tptr_out[nc] = total;
+        info[0] = passes;
+        info[1] = nc;
+    }
+}
+
 // Level skipping (Sec. 3.3): the aggregates of the composed aggregation P = P1 P2
 // are the unions of the first aggregation's groups over each group J of the second.
 // Their members are listed group after group, in the second aggregation's member
@@ -890,7 +1113,11 @@ __device__ inline uint64_t block_sort_keys(uint64_t v, uint64_t *sk)
     return v;
 }
 
-__global__ void __launch_bounds__(kBigThreads) k_coarse_big_rows_acc(const int *__restrict__ big_rows, int nc,
+constexpr int kBigRowBlocks = 256;
+// The blocks take the *nbig listed rows in turn (the count stays on the device: a host
+// read-back would cost more than the idle blocks).
+__global__ void __launch_bounds__(kBigThreads) k_coarse_big_rows_acc(const int *__restrict__ big_rows,
+                                                                     const unsigned *__restrict__ nbig, int nc,
                                                                      const int *__restrict__ rp,
                                                                      const int *__restrict__ ci,
                                                                      const double *__restrict__ va,
@@ -909,121 +1136,123 @@ __global__ void __launch_bounds__(kBigThreads) k_coarse_big_rows_acc(const int *
     __shared__ int sh_tot, sh_out;
     const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
     const uint64_t below = (1ull << lane) - 1ull;
-    const int I = big_rows[blockIdx.x];
-    for (int J = t; J < nc; J += kBigThreads) acc[J] = __longlong_as_double((long long)kUntouched);
-    const int me = aptr[I + 1];
-    for (int m0 = aptr[I]; m0 < me; m0 += kBigThreads) {
-        // block-wide prefix of the row lengths of up to kBigThreads members
-        const int m = m0 + t;
-        int b = 0, len = 0;
-        if (m < me) {
-            const int sidx = members[m];
-            b = rp[sidx];
-            len = rp[sidx + 1] - b;
-        }
-        int incl = len;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const int y = __shfl_up(incl, o, kWave);
-            if (lane >= o) incl += y;
-        }
-        __syncthreads();  // the previous group's readers of mbeg / mexcl / sh_count are done
-        if (lane == kWave - 1) sh_count[w] = incl;
-        __syncthreads();
-        int before = 0;
-        for (int k = 0; k < w; k++) before += sh_count[k];
-        incl += before;
-        mbeg[t] = b;
-        mexcl[t] = incl - len;
-        if (t == kBigThreads - 1) sh_tot = incl;
-        __syncthreads();
-        const int tot = sh_tot;
-        const int nm = (me - m0) < kBigThreads ? (me - m0) : kBigThreads;
-        for (int k0 = 0; k0 < tot; k0 += kBigThreads) {
-            const int k = k0 + t;
-            uint64_t key = ~0ull;
-            double v = 0.0;
-            if (k < tot) {
-                int lo = 0, hi = nm - 1;
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (mexcl[mid] <= k) lo = mid;
-                    else hi = mid - 1;
-                }
-                const int p = mbeg[lo] + (k - mexcl[lo]);
-                key = ((uint64_t)(uint32_t)agg[ci[p]] << 32) | (uint32_t)t;
-                v = va[p];
+    for (unsigned r = blockIdx.x; r < *nbig; r += gridDim.x) {
+        const int I = big_rows[r];
+        for (int J = t; J < nc; J += kBigThreads) acc[J] = __longlong_as_double((long long)kUntouched);
+        const int me = aptr[I + 1];
+        for (int m0 = aptr[I]; m0 < me; m0 += kBigThreads) {
+            // block-wide prefix of the row lengths of up to kBigThreads members
+            const int m = m0 + t;
+            int b = 0, len = 0;
+            if (m < me) {
+                const int sidx = members[m];
+                b = rp[sidx];
+                len = rp[sidx + 1] - b;
             }
-            cv[t] = v;
-            key = block_sort_keys(key, sk);
-            const bool valid = key != ~0ull;
-            const uint32_t J = (uint32_t)(key >> 32);
+            int incl = len;
+#pragma unroll
+            for (int o = 1; o < kWave; o <<= 1) {
+                const int y = __shfl_up(incl, o, kWave);
+                if (lane >= o) incl += y;
+            }
+            __syncthreads();  // the previous group's readers of mbeg / mexcl / sh_count are done
+            if (lane == kWave - 1) sh_count[w] = incl;
             __syncthreads();
-            const double mv = valid ? cv[(uint32_t)key] : 0.0;
-            sk[t] = key;
+            int before = 0;
+            for (int k = 0; k < w; k++) before += sh_count[k];
+            incl += before;
+            mbeg[t] = b;
+            mexcl[t] = incl - len;
+            if (t == kBigThreads - 1) sh_tot = incl;
             __syncthreads();
-            cv[t] = mv;  // values in sorted order
-            const bool head = valid && (t == 0 || (uint32_t)(sk[t - 1] >> 32) != J);
-            const uint64_t hm = __ballot(head);
+            const int tot = sh_tot;
+            const int nm = (me - m0) < kBigThreads ? (me - m0) : kBigThreads;
+            for (int k0 = 0; k0 < tot; k0 += kBigThreads) {
+                const int k = k0 + t;
+                uint64_t key = ~0ull;
+                double v = 0.0;
+                if (k < tot) {
+                    int lo = 0, hi = nm - 1;
+                    while (lo < hi) {
+                        const int mid = (lo + hi + 1) >> 1;
+                        if (mexcl[mid] <= k) lo = mid;
+                        else hi = mid - 1;
+                    }
+                    const int p = mbeg[lo] + (k - mexcl[lo]);
+                    key = ((uint64_t)(uint32_t)agg[ci[p]] << 32) | (uint32_t)t;
+                    v = va[p];
+                }
+                cv[t] = v;
+                key = block_sort_keys(key, sk);
+                const bool valid = key != ~0ull;
+                const uint32_t J = (uint32_t)(key >> 32);
+                __syncthreads();
+                const double mv = valid ? cv[(uint32_t)key] : 0.0;
+                sk[t] = key;
+                __syncthreads();
+                cv[t] = mv;  // values in sorted order
+                const bool head = valid && (t == 0 || (uint32_t)(sk[t - 1] >> 32) != J);
+                const uint64_t hm = __ballot(head);
+                if (lane == 0) sh_count[w] = __popcll(hm);
+                __syncthreads();
+                int hb = 0, nh = 0;
+                for (int q = 0; q < kBigThreads / kWave; q++) {
+                    if (q < w) hb += sh_count[q];
+                    nh += sh_count[q];
+                }
+                if (head) hp[hb + __popcll(hm & below)] = t;
+                if (t == 0) hp[nh] = (tot - k0) < kBigThreads ? (tot - k0) : kBigThreads;
+                __syncthreads();
+                if (t < nh) {  // run t: its values in position order onto acc[J]
+                    const int q = hp[t], qe = hp[t + 1];
+                    const uint32_t JJ = (uint32_t)(sk[q] >> 32);
+                    double a = acc[JJ];
+                    if ((uint64_t)__double_as_longlong(a) == kUntouched) a = 0.0;
+                    int r = q;
+                    for (; r + 16 <= qe; r += 16) {  // LDS reads in flight together, adds in order
+                        double v[16];
+#pragma unroll
+                        for (int u = 0; u < 16; u++) v[u] = cv[r + u];
+#pragma unroll
+                        for (int u = 0; u < 16; u++) a += v[u];
+                    }
+                    for (; r < qe; r++) a += cv[r];
+                    acc[JJ] = a;
+                }
+                __syncthreads();
+            }
+        }
+        // the touched columns in ascending order
+        const int base = tptr[I];
+        if (t == 0) sh_out = 0;
+        for (int J0 = 0; J0 < nc; J0 += kBigThreads) {
+            const int J = J0 + t;
+            double a = 0.0;
+            bool on = false;
+            if (J < nc) {
+                a = acc[J];
+                on = (uint64_t)__double_as_longlong(a) != kUntouched;
+            }
+            const uint64_t hm = __ballot(on);
+            __syncthreads();  // sh_out / sh_count of the previous iteration are read
             if (lane == 0) sh_count[w] = __popcll(hm);
             __syncthreads();
-            int hb = 0, nh = 0;
+            int ob = sh_out, tot = 0;
             for (int q = 0; q < kBigThreads / kWave; q++) {
-                if (q < w) hb += sh_count[q];
-                nh += sh_count[q];
+                if (q < w) ob += sh_count[q];
+                tot += sh_count[q];
             }
-            if (head) hp[hb + __popcll(hm & below)] = t;
-            if (t == 0) hp[nh] = (tot - k0) < kBigThreads ? (tot - k0) : kBigThreads;
-            __syncthreads();
-            if (t < nh) {  // run t: its values in position order onto acc[J]
-                const int q = hp[t], qe = hp[t + 1];
-                const uint32_t JJ = (uint32_t)(sk[q] >> 32);
-                double a = acc[JJ];
-                if ((uint64_t)__double_as_longlong(a) == kUntouched) a = 0.0;
-                int r = q;
-                for (; r + 16 <= qe; r += 16) {  // LDS reads in flight together, adds in order
-                    double v[16];
-#pragma unroll
-                    for (int u = 0; u < 16; u++) v[u] = cv[r + u];
-#pragma unroll
-                    for (int u = 0; u < 16; u++) a += v[u];
-                }
-                for (; r < qe; r++) a += cv[r];
-                acc[JJ] = a;
+            if (on) {
+                const int o = ob + __popcll(hm & below);
+                tcol[base + o] = J;
+                tval[base + o] = a;
             }
             __syncthreads();
-        }
-    }
-    // the touched columns in ascending order
-    const int base = tptr[I];
-    if (t == 0) sh_out = 0;
-    for (int J0 = 0; J0 < nc; J0 += kBigThreads) {
-        const int J = J0 + t;
-        double a = 0.0;
-        bool on = false;
-        if (J < nc) {
-            a = acc[J];
-            on = (uint64_t)__double_as_longlong(a) != kUntouched;
-        }
-        const uint64_t hm = __ballot(on);
-        __syncthreads();  // sh_out / sh_count of the previous iteration are read
-        if (lane == 0) sh_count[w] = __popcll(hm);
-        __syncthreads();
-        int ob = sh_out, tot = 0;
-        for (int q = 0; q < kBigThreads / kWave; q++) {
-            if (q < w) ob += sh_count[q];
-            tot += sh_count[q];
-        }
-        if (on) {
-            const int o = ob + __popcll(hm & below);
-            tcol[base + o] = J;
-            tval[base + o] = a;
+            if (t == 0) sh_out += tot;
         }
         __syncthreads();
-        if (t == 0) sh_out += tot;
+        if (t == 0) cnt[I] = sh_out;
     }
-    __syncthreads();
-    if (t == 0) cnt[I] = sh_out;
 }
 
 // Copy the unique entries of every coarse row into the final CSR and form the
@@ -1358,6 +1587,22 @@ void launch_sum_slots(const unsigned *slots, unsigned *out, hipStream_t s)
     AMG_HIP(hipGetLastError());
 }
 
+bool aggregate_small_fits(int n, int nnz)
+{
+    if (n >= 0xffff || nnz > 0xffff) return false;
+    int dev = 0, lds = 0;
+    AMG_HIP(hipGetDevice(&dev));
+    AMG_HIP(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+    return small_layout(n, nnz).bytes + 256 <= (size_t)lds;
+}
+
+void launch_aggregate_small(int n, int nnz, const int *rp, const int *ci, uint32_t s_l, int cap, int *agg, int *aptr,
+                            int *members, int *tptr, int *info, hipStream_t s)
+{
+    k_aggregate_small<<<1, kAggThreads, small_layout(n, nnz).bytes, s>>>(n, nnz, rp, ci, s_l, cap, agg, aptr, members,
+                                                                         tptr, info);
+    AMG_HIP(hipGetLastError());
+}
 void launch_centre_flags(int n, const int *owner, int *flag, hipStream_t s)
 {
     k_centre_flags<<<grid_for(n), kBlock, 0, s>>>(n, owner, flag);
@@ -1482,14 +1727,13 @@ int coarse_acc_capacity()
     return bytes > 0 ? bytes / (int)sizeof(double) : 0;
 }
 
-void launch_coarse_big_rows_acc(int nbig, const int *big_rows, int nc, const int *rp, const int *ci, const double *va,
-                                const int *agg, const int *aptr, const int *members, const int *tptr, int *tcol,
-                                double *tval, int *cnt, hipStream_t s)
+void launch_coarse_big_rows_acc(const unsigned *nbig, const int *big_rows, int nc, const int *rp, const int *ci,
+                                const double *va, const int *agg, const int *aptr, const int *members,
+                                const int *tptr, int *tcol, double *tval, int *cnt, hipStream_t s)
 {
-    if (nbig <= 0) return;
     const size_t lds = sizeof(double) * (size_t)nc;
-    k_coarse_big_rows_acc<<<nbig, kBigThreads, lds, s>>>(big_rows, nc, rp, ci, va, agg, aptr, members, tptr, tcol,
-                                                         tval, cnt);
+    k_coarse_big_rows_acc<<<std::min(nc, kBigRowBlocks), kBigThreads, lds, s>>>(big_rows, nbig, nc, rp, ci, va, agg, aptr,
+                                                                                members, tptr, tcol, tval, cnt);
     AMG_HIP(hipGetLastError());
 }
 
