@@ -185,6 +185,16 @@ void launch_reciprocals(int m, const int *pos, const double *va, double *dinv, h
 void launch_long_rows(int n, const int *ptr, int lim, int *flags, int *list, int *count_dev, int *scan_tmp,
                       hipStream_t s);
 
+// The chunk table of Rows (ptr over n rows, hub rows longer than lim) on the device:
+// chunks and first must hold a table of up to kMaxLong rows, list (n > kHubScanMax) every
+// row longer than lim; flags n + 1 ints.  A count beyond kMaxLong comes without a table.
+constexpr int kHubScanMax = 16384;
+struct HubCount {
+    int nlong, nchunks;
+};
+void launch_hub_table(int n, const int *ptr, int lim, int *flags, int *list, Chunk *chunks, int *first, HubCount *out,
+                      int *scan_tmp, hipStream_t s);
+
 // Sliced ELLPACK build: width[s] = longest row of slice s (at least 1), for the
 // ceil(n / kWave) slices; then, with the entry offsets ptr (nslices + 1), the copy.
 void launch_sell_widths(int n, const int *rp, int *width, hipStream_t s);

@@ -464,6 +464,87 @@ struct amg_hierarchy {
         return R;
     }
 
+    // The same without a host round trip: the table is built on the device, and
+    // finish_rows reads the counts of all operators at once.  An operator with more
+    // than kMaxLong hub rows falls back to make_rows, as does a hierarchy with a memory
+    // budget (the table's space is an upper bound until the counts are known).
+    struct PendingRows {
+        Rows *dst;
+        int nnz;
+        int *list;
+        amg::Chunk *chunks;
+        int *first;
+        size_t bytes;
+    };
+    static constexpr size_t kKeepTable = 256 << 10;  // larger tables are copied to their exact size
+    std::vector<PendingRows> pending;
+    amg::HubCount *hub_counts = nullptr;
+    void begin_rows(Rows *dst, int n, int nnz, const int *ptr, int G, int *flags, int *scan_tmp)
+    {
+        const int cb = dst->cb;
+        *dst = Rows{};
+        dst->cb = cb;
+        if (pool.budget) {
+            *dst = make_rows(n, ptr, G, flags, scan_tmp);
+            dst->cb = cb;
+            return;
+        }
+        dst->n = n;
+        dst->ptr = ptr;
+        dst->lim = 8 * G;
+        const size_t rows = std::min<size_t>({(size_t)amg::kMaxLong, (size_t)n, (size_t)nnz / dst->lim + 1});
+        const size_t chunks = rows + (size_t)nnz / amg::kChunk + 1;
+        PendingRows p{dst, nnz, nullptr, nullptr, nullptr, 0};
+        if (n > amg::kHubScanMax) p.list = pool.alloc<int>((size_t)nnz / dst->lim + 1);
+        p.bytes = chunks * sizeof(amg::Chunk) + (rows + 1) * sizeof(int);
+        p.chunks = reinterpret_cast<amg::Chunk *>(pool.alloc<char>(p.bytes));
+        p.first = reinterpret_cast<int *>(p.chunks + chunks);
+        amg::launch_hub_table(n, ptr, dst->lim, flags, p.list, p.chunks, p.first, hub_counts + pending.size(), scan_tmp,
+                              stream);
+        pending.push_back(p);
+    }
+    void finish_rows(int *flags, int *scan_tmp)
+    {
+        if (pending.empty()) return;
+        std::vector<amg::HubCount> got(pending.size());
+        to_host(got.data(), hub_counts, pending.size());
+        for (size_t k = 0; k < pending.size(); k++) {
+            PendingRows &p = pending[k];
+            Rows &R = *p.dst;
+            pool.release(p.list);
+            R.nlong = got[k].nlong;
+            R.nchunks = got[k].nchunks;
+            if (R.nlong == 0 || R.nlong > amg::kMaxLong) {
+                pool.release(p.chunks);
+                if (R.nlong > 0) {
+                    const int cb = R.cb;
+                    R = make_rows(R.n, R.ptr, R.lim / 8, flags, scan_tmp);
+                    R.cb = cb;
+                }
+                continue;
+            }
+            if (p.bytes > kKeepTable) {
+                amg::Chunk *chunks = pool.alloc<amg::Chunk>(R.nchunks);
+                int *first = pool.alloc<int>(R.nlong + 1);
+                AMG_HIP(hipMemcpyAsync(chunks, p.chunks, sizeof(amg::Chunk) * R.nchunks, hipMemcpyDeviceToDevice,
+                                       stream));
+                AMG_HIP(hipMemcpyAsync(first, p.first, sizeof(int) * (R.nlong + 1), hipMemcpyDeviceToDevice, stream));
+                drained.push_back(p.chunks);
+                p.chunks = chunks;
+                p.first = first;
+            }
+            R.chunks = p.chunks;
+            R.long_first = p.first;
+            R.chunk_sum = pool.alloc<double>((size_t)R.nchunks * (size_t)opt.max_rhs);  // per right-hand side
+            R.arrive = pool.alloc<unsigned>((size_t)R.nlong * opt.max_rhs);
+            AMG_HIP(hipMemsetAsync(R.arrive, 0, sizeof(unsigned) * R.nlong * opt.max_rhs, stream));
+        }
+        pending.clear();
+    }
+    // blocks released once the stream has drained (another hierarchy's stream may
+    // receive them from the shared cache)
+    std::vector<void *> drained;
+
     void build(const amg_csr &A);
     void finalize_layout();
     void build_sell(int l, const int *rp, const int *ci, const double *va);
@@ -836,7 +917,7 @@ void amg_hierarchy::finalize_layout()
         launch_agg_positions(F.n, F.perm, F.agg_nat, C.pos, F.agg_pos, stream);
     }
     uperm = lev[0].perm;
-    std::vector<void *> drained;
+    hub_counts = pool.budget ? nullptr : pool.alloc<HubCount>(2 * (L + 1));
     for (int l = 0; l <= L; l++) {
         Level &F = lev[l];
         launch_permuted_row_lengths(F.n, F.rp_nat, F.perm, tmp, stream);
@@ -849,9 +930,8 @@ void amg_hierarchy::finalize_layout()
                             stream);
         F.G = lanes_for((double)F.nnz / F.n, F.n);
         const bool natural = l == 0 && L >= 1;  // see below
-        F.A = make_rows(F.n, natural ? F.rp_nat : F.rp, F.G, tmp, scan_tmp);
         F.A.cb = opt.batch_cols > 0 ? opt.batch_cols : 4;
-        AMG_TRACE_MSG("layout level %d: G=%d hub rows=%d chunks=%d", l, F.G, F.A.nlong, F.A.nchunks);
+        begin_rows(&F.A, F.n, F.nnz, natural ? F.rp_nat : F.rp, F.G, tmp, scan_tmp);
         if (l < L) {
             const int nc = lev[l + 1].n;
             // Levels of at least kSmallLevel rows may also hold a sliced ELLPACK copy
@@ -876,10 +956,8 @@ void amg_hierarchy::finalize_layout()
                 F.srp = pool.alloc<int>(nc + 1);
                 launch_gather_int(nc + 1, F.rp, F.seg_ptr, F.srp, stream);
                 F.Gs = lanes_for((double)F.nnz / nc, nc);
-                F.S = make_rows(nc, F.srp, F.Gs, tmp, scan_tmp);
                 F.S.cb = F.A.cb;
-                AMG_TRACE_MSG("layout level %d: super-rows Gs=%d hub rows=%d chunks=%d", l, F.Gs, F.S.nlong,
-                              F.S.nchunks);
+                begin_rows(&F.S, nc, F.nnz, F.srp, F.Gs, tmp, scan_tmp);
                 F.wv = pool.alloc<double>(F.nnz);
                 launch_restriction_weights(F.n, F.rp, F.ci, F.va, F.minv, F.wv, stream);
             } else {
@@ -897,8 +975,6 @@ void amg_hierarchy::finalize_layout()
                     launch_gather_int(F.nnz, F.perm, F.ci, sci, stream);  // sci[e] = perm[ci[e]]
                 }
                 launch_gather_int(F.n, lev[1].pos, F.agg_nat, F.agg_pos, stream);  // natural row -> coarse position
-                // released once the stream has drained (another hierarchy's stream
-                // may receive the blocks from the shared cache)
                 drained.insert(drained.end(), {F.rp, F.ci, F.va, F.minv});
                 F.sci = sci;
                 F.rp = F.rp_nat;
@@ -906,7 +982,7 @@ void amg_hierarchy::finalize_layout()
                 F.va = F.va_nat;
                 F.minv = F.minv_nat;
                 uperm = nullptr;
-                AMG_TRACE_MSG("layout level 0: natural numbering, hub rows=%d", F.A.nlong);
+                AMG_TRACE_MSG("layout level 0: natural numbering");
             }
             if (F.n >= kSmallLevel) F.xs = pool.alloc<double>((size_t)F.n * nr);
             if (F.n < kSmallLevel) {
@@ -930,6 +1006,10 @@ void amg_hierarchy::finalize_layout()
             }
         }
     }
+    finish_rows(tmp, scan_tmp);
+    for (int l = 0; l <= L; l++)
+        AMG_TRACE_MSG("layout level %d: G=%d hub rows=%d chunks=%d; super-rows Gs=%d hub rows=%d chunks=%d", l, lev[l].G,
+                      lev[l].A.nlong, lev[l].A.nchunks, lev[l].Gs, lev[l].S.nlong, lev[l].S.nchunks);
     for (int l = 0; l <= L; l++) {
         Level &F = lev[l];
         F.k64 = KArrays<double>{F.va, F.minv, F.wv, F.rc, F.rt, F.c1, F.c2, F.v1, F.sell_va};
@@ -981,7 +1061,9 @@ void amg_hierarchy::finalize_layout()
     sync();
     pool.release(tmp);
     pool.release(scan_tmp);
+    pool.release(hub_counts);
     for (void *p : drained) pool.release(p);
+    drained.clear();
 }
 
 // The longest run of last levels (not the finest) that one workgroup can hold: every

@@ -21,6 +21,7 @@
 // only claims conflict-free stars, integer counts are exact, and the sums that
 // form A_c run in a fixed order.
 #include "amg_internal.h"
+#include "wave_ops.h"
 
 #include <algorithm>
 #include <climits>
@@ -60,7 +61,6 @@ __device__ inline uint32_t fmix32(uint32_t h)
 
 // 64-bit value of another lane of the same row of 16 (DPP move of both halves):
 // exchange with lane ^ 1 or lane ^ 2 inside a quad, mirror inside 8 or 16 lanes.
-constexpr int kDppQuadXor1 = 0xB1, kDppQuadXor2 = 0x4E, kDppRowHalfMirror = 0x141, kDppRowMirror = 0x140;
 template <int CTRL>
 __device__ inline uint64_t dpp_u64(uint64_t v)
 {
@@ -1349,6 +1349,63 @@ __global__ void __launch_bounds__(kCholThreads) k_cholesky_inverse(int n, double
     }
 }
 
+// The same for at most kInlineCoarse unknowns, in LDS: the factorisation as above, then
+// sixteen lanes per column of the inverse share the sums of the two substitutions (a
+// column's lanes are in one wavefront, so no barriers).  Bound by the chain of 2 n sums
+// and divisions.
+constexpr int kCholLanes = kCholThreads / kInlineCoarse, kCholPitch = kInlineCoarse + 1;
+__global__ void __launch_bounds__(kCholThreads) k_cholesky_inverse_lds(int n, const double *__restrict__ a,
+                                                                       double *__restrict__ inv, int *err)
+{
+    static_assert(kCholLanes == 16, "a column's lanes are a row of 16");
+    __shared__ double l[kInlineCoarse * kCholPitch], x[kInlineCoarse * kCholPitch];  // factor; inverse, column by column
+    __shared__ double piv;
+    __shared__ int bad;
+    const int t = threadIdx.x;
+    if (t == 0) bad = 0;
+    for (int e = t; e < n * n; e += kCholThreads) l[e / n * kCholPitch + e % n] = a[e];
+    __syncthreads();
+    for (int k = 0; k < n; k++) {
+        if (t == 0) {
+            const double d = l[k * kCholPitch + k];
+            if (!(d > 0.0)) {
+                bad = 1;
+                *err = 1;
+            } else {
+                piv = sqrt(d);
+                l[k * kCholPitch + k] = piv;
+            }
+        }
+        __syncthreads();
+        if (bad) return;
+        for (int i = k + 1 + t; i < n; i += kCholThreads) l[i * kCholPitch + k] /= piv;
+        __syncthreads();
+        const int j = k + 1 + (t & (kInlineCoarse - 1));
+        for (int i = k + 1 + t / kInlineCoarse; i < n; i += kCholLanes)
+            if (j <= i) l[i * kCholPitch + j] -= l[i * kCholPitch + k] * l[j * kCholPitch + k];
+        __syncthreads();
+    }
+    const int j = t / kCholLanes, sub = t & (kCholLanes - 1);
+    if (j >= n) return;
+    double *xj = x + j * kCholPitch;
+    for (int i = sub; i < j; i += kCholLanes) xj[i] = 0.0;
+    for (int i = j; i < n; i++) {  // forward: L y = e_j, y_i = 0 for i < j
+        double s = 0.0;
+        for (int k = j + sub; k < i; k += kCholLanes) s += l[i * kCholPitch + k] * xj[k];
+        s = row16_sum(s);
+        if (sub == 0) xj[i] = ((i == j ? 1.0 : 0.0) - s) / l[i * kCholPitch + i];
+        wave_sync();
+    }
+    for (int i = n - 1; i >= 0; i--) {  // backward: L^T x = y
+        double s = 0.0;
+        for (int k = i + 1 + sub; k < n; k += kCholLanes) s += l[k * kCholPitch + i] * xj[k];
+        s = row16_sum(s);
+        if (sub == 0) xj[i] = (xj[i] - s) / l[i * kCholPitch + i];
+        wave_sync();
+    }
+    for (int i = sub; i < n; i += kCholLanes) inv[(size_t)i * n + j] = xj[i];
+}
+
 // Larger coarsest levels: Gauss-Jordan inversion in place, one launch per pivot
 // (no pivoting: every pivot is a Schur complement of an SPD matrix, hence > 0).
 // Step k reads row k and column k as step k-1 left them from rk / ck and writes
@@ -1493,6 +1550,79 @@ __global__ void __launch_bounds__(kBlock) k_long_compact(int n, const int *__res
 // Lanes per row/aggregate for the helper kernels: a wavefront on small levels.
 inline bool wide(int n) { return n < kSmallLevel; }
 
+// Chunk table of an operator's hub rows (see Rows) by one block: the rows longer than
+// lim -- listed in list (list_count of them, ascending), or found here when list is
+// NULL -- cut into chunks of at most kChunk entries.  More than kMaxLong rows: only
+// counted.  (The table used to be built on the host from read-backs, 0.1 ms per level
+// and operator.)
+constexpr int kHubThreads = 1024;
+__global__ void __launch_bounds__(kHubThreads) k_hub_table(int n, const int *__restrict__ ptr, int lim,
+                                                           const int *__restrict__ list,
+                                                           const int *__restrict__ list_count,
+                                                           Chunk *__restrict__ chunks, int *__restrict__ first,
+                                                           HubCount *__restrict__ out)
+{
+    __shared__ int rows[kMaxLong], sh[2][kHubThreads / kWave];
+    const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
+    int set = 0;
+    // exclusive prefix of v over the block; *total = its sum
+    auto prefix = [&](int v, int *total) {
+        int x = v;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int y = __shfl_up(x, o, kWave);
+            if (lane >= o) x += y;
+        }
+        if (lane == kWave - 1) sh[set][w] = x;
+        __syncthreads();
+        int before = x - v, all = 0;
+        for (int k = 0; k < kHubThreads / kWave; k++) {
+            if (k < w) before += sh[set][k];
+            all += sh[set][k];
+        }
+        set ^= 1;
+        *total = all;
+        return before;
+    };
+    int count = 0;
+    if (list) {
+        count = *list_count;
+        for (int k = t; k < min(count, kMaxLong); k += kHubThreads) rows[k] = list[k];
+    } else {
+        for (int i0 = 0; i0 < n; i0 += kHubThreads) {
+            const int i = i0 + t;
+            const int hub = i < n && ptr[i + 1] - ptr[i] > lim ? 1 : 0;
+            int total;
+            const int at = count + prefix(hub, &total);
+            if (hub && at < kMaxLong) rows[at] = i;
+            count += total;
+        }
+    }
+    __syncthreads();
+    int nchunks = 0;
+    if (count <= kMaxLong) {
+        for (int k0 = 0; k0 < count; k0 += kHubThreads) {
+            const int k = k0 + t;
+            int row = 0, b = 0, e = 0;
+            if (k < count) {
+                row = rows[k];
+                b = ptr[row];
+                e = ptr[row + 1];
+            }
+            int total, at = nchunks + prefix((e - b + kChunk - 1) / kChunk, &total);
+            if (k < count) {
+                first[k] = at;
+                for (int c = b; c < e; c += kChunk) chunks[at++] = Chunk{row, c, min(e, c + kChunk), k};
+            }
+            nchunks += total;
+        }
+    }
+    if (t == 0) {
+        if (count <= kMaxLong) first[count] = nchunks;
+        *out = HubCount{count, nchunks};
+    }
+}
+
 // Sliced ELLPACK build (layout in amg_internal.h).  One wavefront per slice: the
 // width is the wavefront's largest row length, at least 1.
 __global__ void __launch_bounds__(kBlock) k_sell_widths(int n, const int *__restrict__ rp, int *__restrict__ width)
@@ -1549,6 +1679,19 @@ void launch_long_rows(int n, const int *ptr, int lim, int *flags, int *list, int
         return;
     }
     k_long_compact<<<grid_for(n), kBlock, 0, s>>>(n, ptr, lim, flags, list);
+    AMG_HIP(hipGetLastError());
+}
+
+void launch_hub_table(int n, const int *ptr, int lim, int *flags, int *list, Chunk *chunks, int *first, HubCount *out,
+                      int *scan_tmp, hipStream_t s)
+{
+    if (n > kHubScanMax) {  // found by the whole chip, then tabulated
+        launch_long_rows(n, ptr, lim, flags, nullptr, flags + n, scan_tmp, s);
+        launch_long_rows(n, ptr, lim, flags, list, nullptr, scan_tmp, s);
+        k_hub_table<<<1, kHubThreads, 0, s>>>(n, ptr, lim, list, flags + n, chunks, first, out);
+    } else {
+        k_hub_table<<<1, kHubThreads, 0, s>>>(n, ptr, lim, nullptr, nullptr, chunks, first, out);
+    }
     AMG_HIP(hipGetLastError());
 }
 
@@ -1753,6 +1896,11 @@ void launch_dense_from_csr(int n, const int *rp, const int *ci, const double *va
 
 void launch_cholesky_inverse(int n, double *a, double *inv, int *err, hipStream_t s)
 {
+    if (n <= kInlineCoarse) {
+        k_cholesky_inverse_lds<<<1, kCholThreads, 0, s>>>(n, a, inv, err);
+        AMG_HIP(hipGetLastError());
+        return;
+    }
     if (n <= kSmallDense) {
         k_cholesky_inverse<<<1, kCholThreads, 0, s>>>(n, a, inv, err);
         AMG_HIP(hipGetLastError());
