@@ -360,6 +360,7 @@ struct Subtree {
     int nu = 2;
     int lds_bytes = 0, over_at = 0, over_bytes = 0;  // the long rows' entries: LDS offset, image size
     int m = 0, nd = 0;       // exact solve: coupled and decoupled unknowns (see CoarseSolve)
+    int dlanes = 0;          // log2 of the lanes per decoupled unknown
     const double *exact_ainv = nullptr, *exact_dinv = nullptr;
     const int *exact_index = nullptr;
     const void *over = nullptr;

@@ -213,8 +213,8 @@ constexpr int kSubExact = kInlineCoarse / 8;  // columns of the inverse per lane
 template <class T, int K>
 struct SubRegs<T, 0, K> {
     double ainv[kSubExact];  // row t / 8, columns t % 8 + 8 u
-    double dinv;             // decoupled unknown t
-    int sbe, dsbe;           // members of coupled unknown t / 8 (this lane's: stride 8) and of decoupled unknown t
+    double dinv;             // decoupled unknown t >> dlanes
+    int sbe, dsbe;           // this lane's members of coupled unknown t / 8 and of that decoupled unknown
     int at;                  // their places, 16 bits each
 };
 
@@ -239,7 +239,9 @@ __device__ __forceinline__ void sub_load_rows(const SubCtx &x, SubRegs<T, D, K> 
 }
 
 // The exact solve of the coarsest level from the residual t of the level above: eight
-// lanes per coupled unknown and row of the inverse, one per decoupled unknown.
+// lanes per coupled unknown and row of the inverse, 2^dlanes per decoupled unknown (as
+// many as the block has: their aggregates hold up to some twenty members, and with one
+// lane each the longest took 1,000 cycles of every visit).
 template <class T>
 __device__ __forceinline__ void sub_exact(const SubCtx &x, const SubRegs<T, 0, 1> &R, const double *t)
 {
@@ -257,9 +259,14 @@ __device__ __forceinline__ void sub_exact(const SubCtx &x, const SubRegs<T, 0, 1
         const double s = group_sum<8>(members(sub_here(R.sbe), 8));
         if (sub == 0) rc[k] = s;  // kInlineCoarse of them, zeros past m
     }
-    if (x.wave * kWave < S.nd) {
-        const double s = members(sub_here(R.dsbe), 1) * R.dinv;
-        if ((int)threadIdx.x < S.nd) c1[(unsigned)sub_here(R.at) >> 16] = s;
+    const int lg = S.dlanes;
+    if (x.wave * kWave < S.nd << lg) {
+        double s = members(sub_here(R.dsbe), 1 << lg);
+        if (lg >= 1) s += dpp_f64<kDppQuadXor1>(s);
+        if (lg >= 2) s += dpp_f64<kDppQuadXor2>(s);
+        if (lg >= 3) s += dpp_f64<kDppRowHalfMirror>(s);
+        const int d = threadIdx.x >> lg;
+        if (d < S.nd && d << lg == (int)threadIdx.x) c1[(unsigned)sub_here(R.at) >> 16] = s * R.dinv;
     }
     __syncthreads();
     if (S.m > 0) {

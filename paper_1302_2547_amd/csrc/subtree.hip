@@ -146,9 +146,10 @@ __global__ void __launch_bounds__(kSubtreeThreads) k_subtree_pack(Subtree S, Sub
         }
         const int J = i < S.m ? (P.cs.idx ? P.cs.idx[i] : i) : 0;
         index[t] = i < S.m ? (seg[J] + sub) | seg[J + 1] << 16 : 0;
-        const int K = t < S.nd ? P.cs.didx[t] : 0;
-        dinv[t] = t < S.nd ? P.cs.dinv[t] : 0.0;
-        index[kSubtreeThreads + t] = t < S.nd ? seg[K] | seg[K + 1] << 16 : 0;
+        const int q = t >> S.dlanes, qs = t & ((1 << S.dlanes) - 1);
+        const int K = q < S.nd ? P.cs.didx[q] : 0;
+        dinv[t] = q < S.nd ? P.cs.dinv[q] : 0.0;
+        index[kSubtreeThreads + t] = q < S.nd ? (seg[K] + qs) | seg[K + 1] << 16 : 0;
         index[2 * kSubtreeThreads + t] = J | K << 16;
         return;
     }
@@ -285,6 +286,8 @@ bool layout_subtree(int count, const int *n, const SubtreeNeed *need, const Coar
         S.width = waves <= kSubWaves ? 1 : (waves <= 2 * kSubWaves ? 2 : 4);
         S.m = cs.m;
         S.nd = cs.nd;
+        S.dlanes = 0;
+        while (S.dlanes < 3 && cs.nd << (S.dlanes + 1) <= kSubtreeThreads) S.dlanes++;
         // the vectors' places are fixed (SubLds); the long rows' other entries come after them
         S.over_at = kSubLevel1 + (top - 1) * 3 * sub_vector(1) + 4 * sub_vector(S.width);
         int64_t at = S.over_at;
