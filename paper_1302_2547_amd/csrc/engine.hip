@@ -260,7 +260,8 @@ struct Level {
     int *agg_pos = nullptr, *seg_ptr = nullptr, *srp = nullptr;  // all but the coarsest level
     int *cagg = nullptr;                                         // coarse unknown of each entry's column
     int *sci = nullptr;  // columns of the super-rows of P^T A (the same array as ci unless level 0 is natural)
-    double *xs = nullptr;  // FP64 iterate of the split post-smoothing (levels >= kSmallLevel rows), n per column
+    // FP64 iterate of the split post-smoothing (levels of at least kSmallLevel rows, those of a batch together)
+    double *xs = nullptr;  // n per column
     Sell sell{};             // sliced ELLPACK copy of A for the large-level sweeps (ptr NULL: none)
     double *sell_va = nullptr;
     size_t sell_slots = 0;
@@ -984,7 +985,8 @@ void amg_hierarchy::finalize_layout()
                 uperm = nullptr;
                 AMG_TRACE_MSG("layout level 0: natural numbering");
             }
-            if (F.n >= kSmallLevel) F.xs = pool.alloc<double>((size_t)F.n * nr);
+            if (F.n >= kSmallLevel || (nr > 1 && (size_t)F.n * nr >= (size_t)kSmallLevel))
+                F.xs = pool.alloc<double>((size_t)F.n * nr);
             if (F.n < kSmallLevel) {
                 F.cagg = pool.alloc<int>(F.nnz);
                 launch_entry_coarse_column(F.nnz, F.ci, F.agg_pos, F.cagg, stream);

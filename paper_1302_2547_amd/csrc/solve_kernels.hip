@@ -783,7 +783,8 @@ __device__ inline double smoothed(double x, double minv, double r, double ax) { 
 // entry that references column t, which at 128^3 and above is bound by the gathers):
 //   k_smooth_start:  x = M^-1 r + P e, one row per thread, stored in FP64;
 //   k_smooth_finish: out = x + M^-1 (r - A x), with the partials of (out, wdot).
-template <class T, int MODE>
+// SMALL: on a level below kSmallLevel rows, the coefficients reduced as k_post_smooth does.
+template <class T, int MODE, bool SMALL>
 __global__ void __launch_bounds__(kBlock) k_smooth_start(int n, const T *__restrict__ minv,
                                                          const T *__restrict__ r,
                                                          const int *__restrict__ agg_pos,
@@ -800,7 +801,7 @@ __global__ void __launch_bounds__(kBlock) k_smooth_start(int n, const T *__restr
     edirect = colv(edirect, nc);
     c1 = colv(c1, nc);
     c2 = colv(c2, nc);
-    const KCoef c = kcycle_coefficients<false>(MODE, kd, second);
+    const KCoef c = kcycle_coefficients<SMALL>(MODE, kd, second);
     if (c.bad && blockIdx.x == 0 && threadIdx.x == 0) atomicOr(flag, 1);
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
         const double e = coarse_value<MODE>(c, edirect, c1, c2, agg_pos[i]);
@@ -877,15 +878,16 @@ __device__ inline bool mm_live(int nc, int c0, const int *gate, bool (&live)[CB]
 // The row loop of visit_rows (large levels) for CB columns: acc(p, s) adds entry
 // p's contribution to the CB sums s; fin(row, s, k) finishes the row for every
 // column (k: hub row index, -1 for an ordinary row), called by one lane.
-template <int G, int CB, class Acc, class Fin>
-__device__ inline void visit_rows_mm(const Rows &R, Acc acc, Fin fin)
+// hub_acc: the same for the entries of a hub row's chunk.
+template <int G, int CB, class Acc, class HubAcc, class Fin>
+__device__ inline void visit_rows_mm(const Rows &R, Acc acc, HubAcc hub_acc, Fin fin)
 {
     const int nlb = R.nchunks < kLongBlocks ? R.nchunks : kLongBlocks;
     if ((int)blockIdx.x < nlb) {
         for (int c = blockIdx.x; c < R.nchunks; c += nlb) {
             const Chunk ch = R.chunks[c];
             double s[CB] = {};
-            for (int p = ch.beg + (int)threadIdx.x; p < ch.end; p += kBlock) acc(p, s);
+            for (int p = ch.beg + (int)threadIdx.x; p < ch.end; p += kBlock) hub_acc(p, s);
             block_sums<CB>(s);
             fin(c, ch, s);
         }
@@ -939,14 +941,14 @@ __global__ void __launch_bounds__(kBlock) k_spmm_dots(Rows R, const int *__restr
             for (int j = 0; j < ND; j++) pc[j * kPartStride + nb + hub] = t[j];
         }
     };
-    visit_rows_mm<G, CB>(
-        R,
-        [&](int p, double (&s)[CB]) {
-            const int j = ci[p];
-            const double a = (double)va[p];
+    auto entry = [&](int p, double (&s)[CB]) {
+        const int j = ci[p];
+        const double a = (double)va[p];
 #pragma unroll
-            for (int k = 0; k < CB; k++) s[k] += a * (double)x[col(k) * n + j];
-        },
+        for (int k = 0; k < CB; k++) s[k] += a * (double)x[col(k) * n + j];
+    };
+    visit_rows_mm<G, CB>(
+        R, entry, entry,
         [&](int row, const Chunk &ch, double (&s)[CB]) {
             if (ch.k < 0) {
 #pragma unroll
@@ -975,14 +977,14 @@ __global__ void __launch_bounds__(kBlock) k_restrict_mm(Rows S, int nf, const in
     bool live[CB];
     if (!mm_live<CB>(nc, c0, gate, live)) return;
     auto col = [&](int k) { return (size_t)(c0 + (k < nc ? k : 0)); };
-    visit_rows_mm<G, CB>(
-        S,
-        [&](int p, double (&s)[CB]) {
-            const int j = ci[p];
-            const double w = (double)wv[p];
+    auto entry = [&](int p, double (&s)[CB]) {
+        const int j = ci[p];
+        const double w = (double)wv[p];
 #pragma unroll
-            for (int k = 0; k < CB; k++) s[k] += w * (double)r[col(k) * nf + j];
-        },
+        for (int k = 0; k < CB; k++) s[k] += w * (double)r[col(k) * nf + j];
+    };
+    visit_rows_mm<G, CB>(
+        S, entry, entry,
         [&](int Q, const Chunk &ch, double (&s)[CB]) {
 #pragma unroll
             for (int k = 0; k < CB; k++) {
@@ -995,8 +997,9 @@ __global__ void __launch_bounds__(kBlock) k_restrict_mm(Rows S, int nf, const in
         });
 }
 
-// k_smooth_finish for CB columns: out = x + M^-1 (r - A x), partials of (out, wdot)
-template <class T, int G, bool DOT, int CB>
+// k_smooth_finish for CB columns: out = x + M^-1 (r - A x), partials of (out, wdot).
+// SMALL: on a level whose single columns take k_post_smooth, with the same bits.
+template <class T, int G, bool DOT, int CB, bool SMALL>
 __global__ void __launch_bounds__(kBlock) k_smooth_finish_mm(Rows R, const int *__restrict__ ci,
                                                              const T *__restrict__ va, const T *__restrict__ minv,
                                                              const T *__restrict__ r, const double *__restrict__ x,
@@ -1029,6 +1032,16 @@ __global__ void __launch_bounds__(kBlock) k_smooth_finish_mm(Rows R, const int *
             const double a = (double)va[p];
 #pragma unroll
             for (int k = 0; k < CB; k++) s[k] += a * x[col(k) * n + j];
+        },
+        [&](int p, double (&s)[CB]) {
+            const int j = ci[p];
+            const double a = (double)va[p];
+#pragma unroll
+            for (int k = 0; k < CB; k++) {
+                const double xj = x[col(k) * n + j];
+                // as the one-launch form of small levels sums a chunk
+                s[k] = SMALL ? __dadd_rn(s[k], __dmul_rn(a, xj)) : s[k] + a * xj;
+            }
         },
         [&](int row, const Chunk &ch, double (&s)[CB]) {
             if (ch.k < 0) {
@@ -2074,10 +2087,21 @@ DotRef launch_post_smooth(Rows R, const int *ci, const T *va, const T *minv, con
         reduce_if_large(1, buf.part, (int)gs.x, buf.final_out, s, ncol, 1, gate);
         return finished(buf.part, (int)gs.x, buf.final_out, 0, 1);
     }
-    if (xtmp && !cagg && R.n >= kSmallLevel && mode >= 0 && mode <= 2) {  // two launches, see k_smooth_start
+    // Two launches (see k_smooth_start) on large levels, and for a batch from the size
+    // on at which its columns together are as many rows: the one-launch form gathers
+    // five values per entry and column and reads the matrix once per column.  Measured
+    // with 8 columns in FP32 storage over the 76,580-, 24,532- and 13,928-row levels of
+    // the 100^3 grid: 33.5 us a visit on average in one launch, 18.4 in two.
+    const bool batch = ncol > 1 && R.cb > 1 && !dot && (int64_t)R.n * ncol >= kSmallLevel;
+    if (xtmp && (batch || (!cagg && R.n >= kSmallLevel)) && mode >= 0 && mode <= 2) {
         const dim3 g1(grid_for(R.n, 1 << 16), ncol);
-#define AMG_START(M) \
-    k_smooth_start<T, M><<<g1, kBlock, 0, s>>>(R.n, minv, r, agg_pos, edirect, c1, c2, kd, xtmp, flag, nc, gate, second)
+#define AMG_START(M)                                                                                                \
+    if (R.n < kSmallLevel)                                                                                          \
+        k_smooth_start<T, M, true><<<g1, kBlock, 0, s>>>(R.n, minv, r, agg_pos, edirect, c1, c2, kd, xtmp, flag, nc, \
+                                                         gate, second);                                             \
+    else                                                                                                            \
+        k_smooth_start<T, M, false><<<g1, kBlock, 0, s>>>(R.n, minv, r, agg_pos, edirect, c1, c2, kd, xtmp, flag, nc, \
+                                                          gate, second)
         switch (mode) {
         case 0: AMG_START(0); break;
         case 1: AMG_START(1); break;
@@ -2102,15 +2126,26 @@ DotRef launch_post_smooth(Rows R, const int *ci, const T *va, const T *minv, con
         }
         if (ncol > 1 && R.cb > 1) {  // batched: CB columns per block
             const dim3 gm(grid.x, (ncol + R.cb - 1) / R.cb);
-#define AMG_FMM(D, CB)                                                                                              \
-    AMG_SWITCH_G(G, (k_smooth_finish_mm<T, kG, D, CB><<<gm, kBlock, 0, s>>>(R, ci, va, minv, r, xtmp, xout, wdot, \
-                                                                            buf.part, ncol, gate)))
+#define AMG_FMM_S(D, CB, SM)                                                                                        \
+    AMG_SWITCH_G(G, (k_smooth_finish_mm<T, kG, D, CB, SM><<<gm, kBlock, 0, s>>>(R, ci, va, minv, r, xtmp, xout, wdot, \
+                                                                                buf.part, ncol, gate)))
+#define AMG_FMM(D, CB) AMG_FMM_S(D, CB, false)
+            if (R.n < kSmallLevel) {
+                switch (R.cb) {
+                case 2: AMG_FMM_S(false, 2, true); break;
+                case 4: AMG_FMM_S(false, 4, true); break;
+                default: AMG_FMM_S(false, 8, true); break;
+                }
+                AMG_HIP(hipGetLastError());
+                return DotRef{nullptr, 0};
+            }
             switch (R.cb) {
             case 2: if (dot) { AMG_FMM(true, 2); } else { AMG_FMM(false, 2); } break;
             case 4: if (dot) { AMG_FMM(true, 4); } else { AMG_FMM(false, 4); } break;
             default: if (dot) { AMG_FMM(true, 8); } else { AMG_FMM(false, 8); } break;
             }
 #undef AMG_FMM
+#undef AMG_FMM_S
         } else if (dot) {
             AMG_SWITCH_G(G, (k_smooth_finish<T, kG, true><<<grid, kBlock, 0, s>>>(R, ci, va, minv, r, xtmp, xout, wdot,
                                                                                 buf.part, gate)));
