@@ -470,12 +470,84 @@ __device__ __forceinline__ bool kcycle(const GroupJob &J, const double *r, doubl
     }
 }
 
-__global__ void __launch_bounds__(kGB) k_group_solve(const GroupJob *__restrict__ jobs, int kcycle_only,
-                                                     GroupResult *__restrict__ res)
+// Moves the coarse levels of a job into the workgroup's LDS, from the coarsest one up
+// while they fit: matrix, index arrays and work vectors; J (a copy of the job, in LDS)
+// then points there.  The K-cycle visits level k 2^k times, and its sweeps are chains of
+// dependent loads: about 150 cycles each from LDS, 500 and more from the L2.  (The
+// coarse index per entry is left out: one more LDS read costs less than its space.)
+__device__ void stage_levels(const GroupJob &src, GroupJob &J, char *pool, int bytes)
 {
+    int at = 0;
+    auto place = [&](size_t count, size_t size) {
+        const int o = at;
+        at += (int)((count * size + 7) / 8 * 8);
+        return pool + o;
+    };
+    for (int l = src.levels - 1; l >= 1; l--) {
+        const GroupLevel &F = src.lev[l];
+        const bool last = l == src.levels - 1;
+        const int n = F.n, nnz = F.nnz, nc = last ? 0 : src.lev[l + 1].n;
+        if (n > bytes / 48 || nnz > bytes / 12) return;
+        const int64_t need = 48 * (int64_t)n + 12 * (int64_t)nnz + 8 * (int64_t)nc + 128;
+        if (at + need > bytes) return;
+        int *rp = reinterpret_cast<int *>(place(n + 1, 4)), *ci = reinterpret_cast<int *>(place(nnz, 4));
+        double *va = reinterpret_cast<double *>(place(nnz, 8)), *minv = reinterpret_cast<double *>(place(n, 8));
+        int *agg = nullptr, *seg = nullptr, *srp = nullptr;
+        if (!last) {
+            agg = reinterpret_cast<int *>(place(n, 4));
+            seg = reinterpret_cast<int *>(place(nc + 1, 4));
+            if (F.srp) srp = reinterpret_cast<int *>(place(nc + 1, 4));
+        }
+        double *vec[4];
+        for (int v = 0; v < 4; v++) vec[v] = reinterpret_cast<double *>(place(n, 8));
+        for (int i = threadIdx.x; i <= n; i += kGB) rp[i] = F.rp[i];
+        for (int e = threadIdx.x; e < nnz; e += kGB) {
+            ci[e] = F.ci[e];
+            va[e] = F.va[e];
+        }
+        for (int i = threadIdx.x; i < n; i += kGB) {
+            minv[i] = F.minv[i];
+            if (!last) agg[i] = F.agg[i];
+        }
+        if (!last) {
+            for (int c = threadIdx.x; c <= nc; c += kGB) {
+                seg[c] = F.seg[c];
+                if (srp) srp[c] = F.srp[c];
+            }
+        }
+        if (threadIdx.x == 0) {
+            GroupLevel &D = J.lev[l];
+            D.rp = rp;
+            D.ci = ci;
+            D.va = va;
+            D.minv = minv;
+            if (!last) {
+                D.agg = agg;
+                D.cagg = nullptr;
+                D.seg = seg;
+                if (srp) D.srp = srp;
+            }
+            D.rc = vec[0];
+            D.c1 = vec[1];
+            D.c2 = vec[2];
+            D.v1 = vec[3];
+        }
+    }
+}
+
+__global__ void __launch_bounds__(kGB) k_group_solve(const GroupJob *__restrict__ jobs, int kcycle_only,
+                                                     GroupResult *__restrict__ res, int pool_bytes)
+{
+    extern __shared__ __align__(16) char pool[];
     __shared__ Shared sh;
+    __shared__ GroupJob J;
     Red red{sh, 0};
-    const GroupJob &J = jobs[blockIdx.x];
+    static_assert(sizeof(GroupJob) % 4 == 0, "copied in words");
+    for (int w = threadIdx.x; w < (int)(sizeof(GroupJob) / 4); w += kGB)
+        reinterpret_cast<int *>(&J)[w] = reinterpret_cast<const int *>(&jobs[blockIdx.x])[w];
+    __syncthreads();
+    stage_levels(jobs[blockIdx.x], J, pool, pool_bytes);
+    __syncthreads();
     const GroupLevel &F = J.lev[0];
     const int n = F.n;
     double *x = J.x, *r = J.r, *z = J.z, *p = J.p, *q = J.q;
@@ -567,7 +639,11 @@ __global__ void __launch_bounds__(kGB) k_group_solve(const GroupJob *__restrict_
 void launch_group_solve(const GroupJob *jobs, int count, int kcycle_only, GroupResult *res, hipStream_t s)
 {
     if (count <= 0) return;
-    k_group_solve<<<count, kGB, 0, s>>>(jobs, kcycle_only, res);
+    int dev = 0, lds = 0;
+    AMG_HIP(hipGetDevice(&dev));
+    AMG_HIP(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+    const int pool = lds - (int)((sizeof(GroupJob) + sizeof(Shared) + 1023) / 1024 * 1024);
+    k_group_solve<<<count, kGB, (size_t)pool, s>>>(jobs, kcycle_only, res, pool);
     AMG_HIP(hipGetLastError());
 }
 
