@@ -550,6 +550,7 @@ struct amg_hierarchy {
     void finalize_layout();
     void build_sell(int l, const int *rp, const int *ci, const double *va);
     void build_subtree();
+    bool build_star();
     void build_single_unknown();
     // the inner residual rt = rcf - (alpha1/rho1) v1 of a parent's first step
     template <class T>
@@ -1096,6 +1097,13 @@ void amg_hierarchy::build_subtree()
     to_host(need, dneed, kSubtreeDepth + 1);
     pool.release(dneed);
     if (!layout_subtree(count, n.data(), need, coarse, mixed ? 4 : 8, subtree_lds_limit(), sub)) return;
+    // A star on its own is left to k_star_visit: no other level would be gained, and
+    // one wavefront here sums the hub's row.  A K-cycle over a star of 101 / 511 / 1,901
+    // rows takes 26 / 27 / 29 us with it, 29 / 33 / 57 us with k_subtree.
+    if (sub.levels == 2 && build_star()) {
+        sub = Subtree{};
+        return;
+    }
     const size_t bytes = subtree_bytes(sub, mixed ? 4 : 8);
     if (pool.budget && pool.used + bytes > pool.budget) return;
     sub.nu = opt.kcycle_inner;
@@ -1109,36 +1117,46 @@ void amg_hierarchy::build_subtree()
         AMG_TRACE_MSG("level %d: %d rows in %d wavefront slots, %d long", L - d, n[d], need[d].waves, need[d].nover);
 }
 
-// A single coarse unknown below level L-1 (L >= 2, not in the subtree): the level is
-// a star, whose coarse correction one block forms where it is small enough; else the
-// restriction is the row vector om (launch_single_unknown_weights).
+// Level L-1 over a single coarse unknown, as the star whose coarse correction one block
+// forms (false: another shape, or too large a level).
+bool amg_hierarchy::build_star()
+{
+    using namespace amg;
+    const int L = levels() - 1;
+    if (L < 2 || lev[L].n != 1) return false;
+    Level &F = lev[L - 1];
+    if (F.star.n) return true;
+    const size_t value = mixed ? sizeof(float) : sizeof(double);
+    const size_t rows = ((size_t)F.n * value + 15) / 16 * 16;
+    const size_t bytes = 2 * rows + sizeof(StarExtra) + sizeof(StarInfo);
+    if (F.n < 3 || F.n > kStarMaxRows || (pool.budget && pool.used + bytes > pool.budget)) return false;
+    char *at = pool.alloc<char>(bytes);
+    StarExtra *ext = reinterpret_cast<StarExtra *>(at + 2 * rows);
+    StarInfo *dinfo = reinterpret_cast<StarInfo *>(ext + 1), info{};
+    if (mixed)
+        launch_star_layout<float>(F.n, F.rp, F.ci, F.k32.va, reinterpret_cast<float *>(at),
+                                  reinterpret_cast<float *>(at + rows), ext, dinfo, stream);
+    else
+        launch_star_layout<double>(F.n, F.rp, F.ci, F.va, reinterpret_cast<double *>(at),
+                                   reinterpret_cast<double *>(at + rows), ext, dinfo, stream);
+    to_host(&info, dinfo, 1);
+    if (!info.ok) {
+        pool.release(at);
+        return false;
+    }
+    F.star = StarLayout{F.n, info.hub, info.extra, at, at + rows, ext};
+    AMG_TRACE_MSG("level %d: star of %d rows, %d entries between leaves, in one block", L - 1, F.n, info.extra);
+    return true;
+}
+
+// A single coarse unknown below level L-1 (L >= 2, not in the subtree): a star in one
+// block, else the restriction is the row vector om (launch_single_unknown_weights).
 void amg_hierarchy::build_single_unknown()
 {
     using namespace amg;
     const int L = levels() - 1;
-    if (L < 2 || sub_top || lev[L].n != 1 || lev[L - 1].nnz > (1 << 24)) return;
+    if (L < 2 || sub_top || lev[L].n != 1 || lev[L - 1].nnz > (1 << 24) || build_star()) return;
     Level &F = lev[L - 1];
-    const size_t value = mixed ? sizeof(float) : sizeof(double);
-    const size_t rows = ((size_t)F.n * value + 15) / 16 * 16;
-    const size_t bytes = 2 * rows + sizeof(StarExtra) + sizeof(StarInfo);
-    if (F.n >= 3 && F.n <= kStarMaxRows && !(pool.budget && pool.used + bytes > pool.budget)) {
-        char *at = pool.alloc<char>(bytes);
-        StarExtra *ext = reinterpret_cast<StarExtra *>(at + 2 * rows);
-        StarInfo *dinfo = reinterpret_cast<StarInfo *>(ext + 1), info{};
-        if (mixed)
-            launch_star_layout<float>(F.n, F.rp, F.ci, F.k32.va, reinterpret_cast<float *>(at),
-                                      reinterpret_cast<float *>(at + rows), ext, dinfo, stream);
-        else
-            launch_star_layout<double>(F.n, F.rp, F.ci, F.va, reinterpret_cast<double *>(at),
-                                       reinterpret_cast<double *>(at + rows), ext, dinfo, stream);
-        to_host(&info, dinfo, 1);
-        if (info.ok) {
-            F.star = StarLayout{F.n, info.hub, info.extra, at, at + rows, ext};
-            AMG_TRACE_MSG("level %d: star of %d rows, %d entries between leaves, in one block", L - 1, F.n, info.extra);
-            return;
-        }
-        pool.release(at);
-    }
     F.omega = pool.alloc<double>(F.n);
     launch_single_unknown_weights(F.n, F.rp, F.ci, F.va, F.minv, F.omega, stream);
     F.d_om = dot_buf();
