@@ -16,6 +16,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <mutex>
 #include <new>
@@ -331,9 +332,10 @@ struct amg_hierarchy {
     float *r32 = nullptr, *z32 = nullptr;
     KDots kd0{};             // dots of the finest visit's coarse correction (for timing)
     int mode0 = -1;          // how its post-smoothing takes the correction (-1: no K-cycle yet)
-    int *flag = nullptr;     // bit 0: Krylov breakdown
+    int *flag = nullptr;     // bit 0: Krylov breakdown; just before scal (both read back at once)
+    bool flag_clear = false; // known to be zero: no launch since it was read or cleared
     struct Graphs {
-        hipGraphExec_t k = nullptr, step = nullptr;
+        hipGraphExec_t k = nullptr, iteration = nullptr;  // the K-cycle alone; with the outer step
     };
     std::map<int, Graphs> graphs;  // per batch width (an entry without graphs: launch eagerly)
     static constexpr int kMaxGraphDepth = 12;
@@ -350,7 +352,22 @@ struct amg_hierarchy {
         }
         return v;
     }
-    double *host = nullptr;  // pinned: readbacks
+    double *host = nullptr;  // pinned: the flag, the scalars, other readbacks
+    void clear_flag()
+    {
+        if (!flag_clear) AMG_HIP(hipMemsetAsync(flag, 0, sizeof(int), stream));
+        flag_clear = false;
+    }
+    // the flag (in host[0]) and the scalars of ncol columns (from host + 1)
+    bool read_step(int ncol)
+    {
+        AMG_HIP(hipMemcpyAsync(host, scal - 1, sizeof(double) * ((size_t)amg::kScalCol * ncol + 1),
+                               hipMemcpyDeviceToHost, stream));
+        sync();
+        int f;
+        std::memcpy(&f, host, sizeof(int));
+        return f != 0;
+    }
     int *host_i = nullptr;
     // Per right-hand side of the outer iteration (max_rhs ints each, device and a
     // pinned host copy): active (still iterating), restart (the next direction is
@@ -367,7 +384,7 @@ struct amg_hierarchy {
         AMG_TRACE_MSG("free: start");
         if (stream) (void)hipStreamSynchronize(stream);
         for (auto &kv : graphs)
-            for (hipGraphExec_t g : {kv.second.k, kv.second.step})
+            for (hipGraphExec_t g : {kv.second.k, kv.second.iteration})
                 if (g) (void)hipGraphExecDestroy(g);
         AMG_TRACE_MSG("free: graphs destroyed");
         pool.release_all();
@@ -564,7 +581,8 @@ struct amg_hierarchy {
     void run_kcycle(int ncol);
     void run_step(int ncol);
     void upload_masks();
-    void capture_graphs(int ncol);
+    bool graphs_wanted() const;
+    hipGraphExec_t captured(hipGraphExec_t Graphs::*which, int ncol);
     // lanes per row of the bandwidth-bound levels, by measurement (once per hierarchy)
     bool tuned = false;
     void autotune(int ncol);
@@ -580,8 +598,8 @@ void amg_hierarchy::build(const amg_csr &A)
     AMG_HIP(hipEventCreate(&ev0));
     AMG_HIP(hipEventCreate(&ev1));
     const size_t nscal = (size_t)amg::kScalCol * (size_t)opt.max_rhs;  // per-column device scalars
-    AMG_HIP(hipHostMalloc((void **)&host, (nscal + 64) * sizeof(double), hipHostMallocDefault));
-    host_i = reinterpret_cast<int *>(host + nscal + 32);
+    AMG_HIP(hipHostMalloc((void **)&host, (nscal + 65) * sizeof(double), hipHostMallocDefault));
+    host_i = reinterpret_cast<int *>(host + nscal + 33);
     AMG_HIP(hipHostMalloc((void **)&host_mask, 3 * (size_t)opt.max_rhs * sizeof(int), hipHostMallocDefault));
     AMG_HIP(hipEventRecord(ev0, stream));
 
@@ -1057,9 +1075,9 @@ void amg_hierarchy::finalize_layout()
     d_rr = dot_buf();
     d_zq = dot_buf();
     d_res = dot_buf();
-    scal = pool.alloc<double>((size_t)amg::kScalCol * nr);
-    flag = pool.alloc<int>(1);
-    AMG_HIP(hipMemsetAsync(flag, 0, sizeof(int), stream));
+    scal = pool.alloc<double>((size_t)amg::kScalCol * nr + 1) + 1;
+    flag = reinterpret_cast<int *>(scal - 1);
+    AMG_HIP(hipMemsetAsync(flag, 0, sizeof(double), stream));
     mask = pool.alloc<int>(3 * nr);
     sync();
     pool.release(tmp);
@@ -1322,21 +1340,17 @@ DotRef amg_hierarchy::kcycle(int k, const T *rr, T *xx, const T *wdot, const RtS
                                  FK.sva, gate, second);
 }
 
-// One outer iteration is split in two replayable pieces, both run for the active
-// right-hand sides only (mask[0 .. max_rhs)):
+// One outer iteration, run for the active right-hand sides only (mask[0 .. max_rhs)):
 //   K    : z = B r, with (z, A p) for the direction update
 //   step : p = z (restart) or p = z + beta p; q = A p, (p, q), (p, r);
 //          x += alpha p, r -= alpha q; (r, r)
 void amg_hierarchy::run_kcycle(int ncol)
 {
     using namespace amg;
-    const auto g = graphs.find(ncol);
     // one right-hand side is always active while it iterates: no gate (its load
     // would open every kernel of the cycle)
     const int *active = ncol > 1 ? mask : nullptr;
-    if (g != graphs.end() && g->second.k) {
-        AMG_HIP(hipGraphLaunch(g->second.k, stream));
-    } else if (mixed) {  // scal[c * kScalCol] holds (r, r) of column c
+    if (mixed) {  // scal[c * kScalCol] holds (r, r) of column c
         const int n = lev[0].n;
         launch_to_inner(n, r, scal, r32, stream, ncol);
         kcycle<float>(0, r32, z32, nullptr, nullptr, ncol, active);
@@ -1349,11 +1363,6 @@ void amg_hierarchy::run_kcycle(int ncol)
 void amg_hierarchy::run_step(int ncol)
 {
     using namespace amg;
-    const auto g = graphs.find(ncol);
-    if (g != graphs.end() && g->second.step) {
-        AMG_HIP(hipGraphLaunch(g->second.step, stream));
-        return;
-    }
     Level &F = lev[0];
     const int *active = ncol > 1 ? mask : nullptr, *restart = mask + opt.max_rhs;
     // before the first step dr_pq is unset; every column restarts then and reads no products
@@ -1525,6 +1534,7 @@ void amg_hierarchy::autotune(int ncol)
 {
     if (tuned || !opt.autotune) return;
     tuned = true;
+    flag_clear = false;
     for (int l = 0; l + 1 < levels(); l++) {
         if (lev[l].n < amg::kSmallLevel || lev[l].omega) continue;
         if (mixed) autotune_level<float>(l, ncol);
@@ -1532,14 +1542,20 @@ void amg_hierarchy::autotune(int ncol)
     }
 }
 
-void amg_hierarchy::capture_graphs(int ncol)
+// The K-cycle visits level k 2^k times, so its graph has about 6 (2^L - 1) nodes (L
+// the top of the one-workgroup levels where there are such); deep hierarchies (small
+// aggregates) are launched eagerly instead.
+bool amg_hierarchy::graphs_wanted() const
 {
-    // The K-cycle visits level k 2^k times, so its graph has about 6 (2^L - 1)
-    // nodes (L the top of the one-workgroup levels where there are such); deep hierarchies (small aggregates) are launched eagerly instead.
-    if (!opt.use_graph || graphs.count(ncol)) return;
-    Graphs &G = graphs[ncol];
-    const int L = levels() - 1;
-    if ((sub_top ? sub_top : L) > kMaxGraphDepth) return;
+    return opt.use_graph && (sub_top ? sub_top : levels() - 1) <= kMaxGraphDepth;
+}
+
+// The graph of the K-cycle, or of a whole outer iteration (one launch for both pieces
+// spares a small problem several microseconds an iteration), captured at its first use.
+hipGraphExec_t amg_hierarchy::captured(hipGraphExec_t Graphs::*which, int ncol)
+{
+    hipGraphExec_t &have = graphs[ncol].*which;
+    if (have) return have;
     // out NULL: record the body's launches and drop them (nothing runs)
     auto capture = [&](auto &&body, hipGraphExec_t *out) {
         hipGraph_t g = nullptr;
@@ -1556,18 +1572,24 @@ void amg_hierarchy::capture_graphs(int ncol)
         (void)hipGraphDestroy(g);
         AMG_HIP(e);
     };
-    hipGraphExec_t gk = nullptr, gs = nullptr;
-    AMG_TRACE_MSG("capturing K-cycle graph (%d right-hand sides)", ncol);
-    capture([&] { run_kcycle(ncol); }, &gk);
-    AMG_TRACE_MSG("capturing outer-iteration graph");
-    // the step's direction update reads the products of the previous step, whose
-    // partial-sum set its own launch of A p fixes: a first capture (never launched)
-    // records that set, the second uses it
-    capture([&] { run_step(ncol); }, nullptr);
-    capture([&] { run_step(ncol); }, &gs);
-    AMG_TRACE_MSG("graphs ready");
-    G.k = gk;
-    G.step = gs;
+    hipGraphExec_t exec = nullptr;
+    if (which == &Graphs::k) {
+        AMG_TRACE_MSG("capturing K-cycle graph (%d right-hand sides)", ncol);
+        capture([&] { run_kcycle(ncol); }, &exec);
+    } else {
+        AMG_TRACE_MSG("capturing outer-iteration graph (%d right-hand sides)", ncol);
+        // the step's direction update reads the products of the previous step, whose
+        // partial-sum set its own launch of A p fixes: a first capture (never launched)
+        // records that set, the second uses it
+        capture([&] { run_step(ncol); }, nullptr);
+        capture([&] {
+            run_kcycle(ncol);
+            run_step(ncol);
+        }, &exec);
+    }
+    AMG_TRACE_MSG("graph ready");
+    have = exec;
+    return exec;
 }
 
 // Outer flexible CG over ncol right-hand sides at once (column c of b_user at
@@ -1584,8 +1606,9 @@ amg_status amg_hierarchy::solve(int ncol, const double *b_user, int ldb, double 
     AMG_TRACE_MSG("solve: start (%d right-hand sides)", ncol);
     AMG_HIP(hipEventRecord(ev0, stream));
     autotune(ncol);
-    capture_graphs(ncol);
-    AMG_HIP(hipMemsetAsync(flag, 0, sizeof(int), stream));
+    const hipGraphExec_t iteration = graphs_wanted() ? captured(&Graphs::iteration, ncol) : nullptr;
+    clear_flag();
+    double *host = this->host + 1;  // the scalars
     launch_gather(n, b_user, uperm, b, stream, ncol, ldb, n);
     launch_gather(n, x_user, uperm, x, stream, ncol, ldx, n);
     const int nr = opt.max_rhs;
@@ -1628,13 +1651,16 @@ amg_status amg_hierarchy::solve(int ncol, const double *b_user, int ldb, double 
     amg_status st = AMG_ERR_NOT_CONVERGED;
     while (!all_done() && it < opt.max_iters) {
         upload_masks();
-        run_kcycle(ncol);  // z = B r
-        run_step(ncol);
-        AMG_HIP(hipMemcpyAsync(host, scal, sizeof(double) * kScalCol * ncol, hipMemcpyDeviceToHost, stream));
-        AMG_HIP(hipMemcpyAsync(host_i, flag, sizeof(int), hipMemcpyDeviceToHost, stream));
-        sync();
+        if (iteration) {
+            AMG_HIP(hipGraphLaunch(iteration, stream));
+        } else {
+            run_kcycle(ncol);  // z = B r
+            run_step(ncol);
+        }
+        const bool broken = read_step(ncol);
         it++;
-        if (host_i[0]) {
+        flag_clear = !broken;
+        if (broken) {
             st = AMG_ERR_BREAKDOWN;
             break;
         }
@@ -1960,20 +1986,33 @@ amg_status kcycle_columns(amg_hierarchy *h, int ncol, const double *r, int ldr, 
     return guarded([&]() {
         const Level &F = h->lev[0];
         h->autotune(ncol);
-        h->capture_graphs(ncol);
-        AMG_HIP(hipMemsetAsync(h->flag, 0, sizeof(int), h->stream));
-        for (int c = 0; c < 3 * h->opt.max_rhs; c++) h->host_mask[c] = c < ncol ? 1 : 0;  // every column active
-        h->upload_masks();
-        amg::launch_gather(F.n, r, h->uperm, h->r, h->stream, ncol, ldr, F.n);
-        if (h->mixed) {  // the mixed K-cycle reads (r, r) of column c from scal[c * kScalCol]
-            const DotRef rr = amg::launch_dot(F.n, h->r, h->r, h->d_res, h->stream, ncol);
-            amg::launch_reduce(rr, h->scal, h->stream, ncol);
+        // Where all levels but the finest are one launch, the cycle is three: they run on
+        // the caller's vectors (which must not overlap: z is written while r is read)
+        // instead of between copies of them.
+        const std::less<const double *> before;
+        const bool apart = !before(z, r + F.n) || !before(r, z + F.n);
+        const bool short_cycle = h->sub_top == 1 || (h->levels() == 3 && h->lev[1].star.n > 0);
+        if (ncol == 1 && !h->mixed && !h->uperm && short_cycle && apart) {
+            h->clear_flag();
+            h->kcycle<double>(0, r, z, nullptr, nullptr, 1);
+        } else {
+            const hipGraphExec_t graph =
+                h->graphs_wanted() ? h->captured(&amg_hierarchy::Graphs::k, ncol) : nullptr;
+            h->clear_flag();
+            for (int c = 0; c < 3 * h->opt.max_rhs; c++) h->host_mask[c] = c < ncol ? 1 : 0;  // every column active
+            h->upload_masks();
+            amg::launch_gather(F.n, r, h->uperm, h->r, h->stream, ncol, ldr, F.n);
+            if (h->mixed) {  // the mixed K-cycle reads (r, r) of column c from scal[c * kScalCol]
+                const DotRef rr = amg::launch_dot(F.n, h->r, h->r, h->d_res, h->stream, ncol);
+                amg::launch_reduce(rr, h->scal, h->stream, ncol);
+            }
+            if (graph) AMG_HIP(hipGraphLaunch(graph, h->stream));
+            else h->run_kcycle(ncol);
+            amg::launch_scatter(F.n, h->z, h->uperm, z, h->stream, ncol, F.n, ldz);
         }
-        h->run_kcycle(ncol);
-        amg::launch_scatter(F.n, h->z, h->uperm, z, h->stream, ncol, F.n, ldz);
-        AMG_HIP(hipMemcpyAsync(h->host_i, h->flag, sizeof(int), hipMemcpyDeviceToHost, h->stream));
-        h->sync();
-        return h->host_i[0] ? AMG_ERR_BREAKDOWN : AMG_OK;
+        const bool broken = h->read_step(0);
+        h->flag_clear = !broken;
+        return broken ? AMG_ERR_BREAKDOWN : AMG_OK;
     });
 }
 }  // namespace
@@ -2015,6 +2054,7 @@ amg_status amg_time_smoother(amg_hierarchy *h, int32_t reps, double *avg_us, dou
                                                 C.n, 1, F.xs, F.sl(), F.k64.sva);
             }
         };
+        h->flag_clear = false;
         launch();
         AMG_HIP(hipEventRecord(h->ev0, h->stream));
         for (int k = 0; k < reps; k++) launch();

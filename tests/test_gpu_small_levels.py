@@ -176,3 +176,25 @@ def test_batched_mid_level_bits(amg, columns, precision):
         h.kcycle(r[c], one)
         assert torch.equal(one, z[c]), c
     h.close()
+
+
+# A cycle of three launches runs on the caller's vectors unless they overlap: apart,
+# at odd offsets, the same and shifted against each other the result has the same bits.
+@pytest.mark.parametrize("problem", ["held", "star"])
+def test_short_cycle_on_the_callers_vectors(amg, problem):
+    csr = inputs.grid_laplacian((33, 31), jitter=0.1, seed=3) if problem == "held" else star_graph(300)
+    n = len(csr[0]) - 1
+    b = np.random.default_rng(7).standard_normal(n)
+    with amg.Hierarchy(*(torch.from_numpy(v).cuda() for v in csr)) as h:
+        want = torch.empty(n, dtype=torch.float64, device="cuda")
+        h.kcycle(torch.from_numpy(b).cuda(), want)
+        for at_r, at_z in [(0, n), (1, n + 3), (n + 5, 1), (0, 0), (1, 0), (0, 1), (0, n - 1), (n - 1, 0)]:
+            room = torch.full((2 * n + 8,), 7.0, dtype=torch.float64, device="cuda")
+            r, z = room[at_r : at_r + n], room[at_z : at_z + n]
+            r.copy_(torch.from_numpy(b))
+            h.kcycle(r, z)
+            assert torch.equal(z, want), (at_r, at_z)
+        x = torch.zeros(n, dtype=torch.float64, device="cuda")
+        h.solve(want, x, 1e-8)
+        h.kcycle(torch.from_numpy(b).cuda(), x)  # after a solve, whose graph holds the cycle too
+        assert torch.equal(x, want)
