@@ -453,7 +453,8 @@ __global__ void __launch_bounds__(kBlock) k_member_fill(int nc, const int *__res
 // Alg. 2, the numbering of Sec. 5.1 and the member lists, with the pattern, the keys
 // and the maxima in LDS (16-bit indices).  A level of a thousand rows takes about ten
 // passes; launched one by one, with the count of processed vertices read back, they
-// and the scans around them cost 0.25-0.4 ms of latency for some 20 us of work.  The
+// and the scans around them cost 0.25-0.4 ms of latency for some 20 us of work; here
+// 50-77 us, a chain of LDS reads and barriers.  Used wherever the level fits in LDS.  The
 // decisions are those of k_mis_max1 / k_mis_select_claim: every pass reads the keys and
 // maxima of the one before, and the order in which rows are served does not matter.
 constexpr int kAggThreads = 1024, kAggLanes = 4, kAggLim = 64;
@@ -1352,7 +1353,7 @@ __global__ void __launch_bounds__(kCholThreads) k_cholesky_inverse(int n, double
 // The same for at most kInlineCoarse unknowns, in LDS: the factorisation as above, then
 // sixteen lanes per column of the inverse share the sums of the two substitutions (a
 // column's lanes are in one wavefront, so no barriers).  Bound by the chain of 2 n sums
-// and divisions.
+// and divisions: 39-59 us, against 213-298 in global memory.
 constexpr int kCholLanes = kCholThreads / kInlineCoarse, kCholPitch = kInlineCoarse + 1;
 __global__ void __launch_bounds__(kCholThreads) k_cholesky_inverse_lds(int n, const double *__restrict__ a,
                                                                        double *__restrict__ inv, int *err)
@@ -1553,8 +1554,8 @@ inline bool wide(int n) { return n < kSmallLevel; }
 // Chunk table of an operator's hub rows (see Rows) by one block: the rows longer than
 // lim -- listed in list (list_count of them, ascending), or found here when list is
 // NULL -- cut into chunks of at most kChunk entries.  More than kMaxLong rows: only
-// counted.  (The table used to be built on the host from read-backs, 0.1 ms per level
-// and operator.)
+// counted.  2.5-3.4 us, bound by latency; built on the host from read-backs, the tables
+// of a level's two operators took 0.1-0.2 ms.
 constexpr int kHubThreads = 1024;
 __global__ void __launch_bounds__(kHubThreads) k_hub_table(int n, const int *__restrict__ ptr, int lim,
                                                            const int *__restrict__ list,

