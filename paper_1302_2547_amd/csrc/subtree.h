@@ -285,22 +285,24 @@ __device__ __forceinline__ void sub_exact(const SubCtx &x, const SubRegs<T, 0, 1
 
 // alpha1 / rho1 of a first step from its products d = (c1, A c1), (c1, rc): 0 and the
 // breakdown flag when A turns out not to be SPD; a zero coarse residual gives c1 = 0
-// and no correction.
-__device__ __forceinline__ double sub_first(const SubCtx &x, const double (&d)[4], double *r1)
+// and no correction.  *rho: rho1, or 0 where there is no correction.
+__device__ __forceinline__ double sub_first(const SubCtx &x, const double (&d)[4], double *rho)
 {
     const double rho1 = d[0], alpha1 = d[1];
     const bool ok = rho1 > 0.0;
     if (threadIdx.x == 0 && !ok && !(rho1 == 0.0 && alpha1 == 0.0)) atomicOr(x.flag, 1);
-    *r1 = lane_value(ok ? 1.0 / rho1 : 0.0, 0);
+    *rho = lane_value(ok ? rho1 : 0.0, 0);
     return lane_value(ok ? alpha1 / rho1 : 0.0, 0);
 }
 // The correction's coefficients after the second step: d = (c2, A c2), (c2, rt), (c2, A c1).
-__device__ __forceinline__ SubCoef sub_second(const SubCtx &x, const double (&d)[4], double q1, double r1)
+// gamma / rho1 is a quotient, not a product with 1 / rho1, which is infinite for a
+// subnormal rho1 (residuals of about 1e-154).
+__device__ __forceinline__ SubCoef sub_second(const SubCtx &x, const double (&d)[4], double q1, double rho1)
 {
     const double beta = d[0], alpha2 = d[1], gamma = d[2];
     SubCoef c{q1, 0.0, true};
-    if (r1 != 0.0) {
-        const double g1 = gamma * r1, rho2 = beta - gamma * g1;
+    if (rho1 != 0.0) {
+        const double g1 = gamma / rho1, rho2 = beta - gamma * g1;
         if (rho2 > 0.0) {
             c.a2 = lane_value(alpha2 / rho2, 0);
             c.a1 = q1 - g1 * c.a2;
@@ -369,7 +371,7 @@ __device__ __forceinline__ SubCoef sub_correct(const SubCtx &x, SubRegs<T, D, K>
         });
         __syncthreads();
         SubCoef c{0.0, 0.0, false};
-        double q = 0.0, r1 = 0.0;
+        double q = 0.0, rho1 = 0.0;
 #pragma unroll 1
         for (int step = 0; step < 2; step++) {
             const SubCoef e = sub_correct<T, D - 1, 1>(x, R.below, c2, K * kSubtreeThreads);
@@ -404,12 +406,12 @@ __device__ __forceinline__ SubCoef sub_correct(const SubCtx &x, SubRegs<T, D, K>
             __syncthreads();
             if (step) {
                 sub_totals(x.sh.part[0], d);
-                return sub_second(x, d, q, r1);
+                return sub_second(x, d, q, rho1);
             }
             // q is reduced while A M^-1 y is formed
             if (x.S.nu == 2) each([&](SubRow<T> &w, int k, int slot) { s[k] = w.times(x, F, g, slot); });
             sub_totals(x.sh.part[0], d);
-            q = sub_first(x, d, &r1);
+            q = sub_first(x, d, &rho1);
             c = SubCoef{q, 0.0, false};
             if (x.S.nu == 1) break;
             double rcrc = 0.0, rtrt = 0.0;
