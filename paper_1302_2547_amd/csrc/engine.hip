@@ -619,7 +619,7 @@ void amg_hierarchy::build(const amg_csr &A)
         AMG_HIP(hipMemcpyAsync(L0.va_nat, A.values, sizeof(double) * (size_t)nnz0, hipMemcpyDeviceToDevice, stream));
     }
     // setup scratch, sized by the finest level and released at the end of setup
-    int *ibuf = pool.alloc<int>(16);  // 0 err, 2 big_count, 3 nc, 4 total, 5 nnz_c, 8.. pass counts
+    int *ibuf = pool.alloc<int>(12);  // 0 err, 2 big_count, 3 nc, 4 total, 5 nnz_c, 8.. four pass counts
     uint64_t *key = pool.alloc<uint64_t>(n0);
     uint64_t *m1 = pool.alloc<uint64_t>(n0);
     int *owner = pool.alloc<int>(n0);
@@ -636,7 +636,7 @@ void amg_hierarchy::build(const amg_csr &A)
     unsigned *done = pool.alloc<unsigned>((size_t)kDoneSlots * kDoneStride);  // per-block-group counters
     unsigned *big_count = reinterpret_cast<unsigned *>(ibuf + 2);
 
-    AMG_HIP(hipMemsetAsync(ibuf, 0, 16 * sizeof(int), stream));
+    AMG_HIP(hipMemsetAsync(ibuf, 0, 12 * sizeof(int), stream));
     launch_validate_csr(n0, nnz0, lev[0].rp_nat, lev[0].ci_nat, lev[0].va_nat, ibuf, stream);
     if (read_int(ibuf) != 0) throw Error(AMG_ERR_INVALID_MATRIX, "invalid CSR");
     launch_inverse_diagonal(n0, lev[0].rp_nat, lev[0].ci_nat, lev[0].va_nat, smoother_weight(), lev[0].minv_nat,
@@ -656,7 +656,10 @@ void amg_hierarchy::build(const amg_csr &A)
         int passes = 0, nc = 0;
         const bool fits = !pool.budget || pool.used + 3 * sizeof(int) * ((size_t)n + 1) <= pool.budget;
         if (fits && aggregate_small_fits(n, nnz)) {  // in one launch
-            int *agg = pool.alloc<int>(n), *aptr = pool.alloc<int>(n + 1), *members = pool.alloc<int>(n);
+            // nc is known only after the launch: aptr keeps room for n aggregates, or is
+            // copied to its exact size where a memory budget counts it
+            int *agg = pool.alloc<int>(n), *members = pool.alloc<int>(n);
+            int *aptr = pool.budget ? cid : pool.alloc<int>(n + 1);
             launch_aggregate_small(n, nnz, F.rp_nat, F.ci_nat, s_l, opt.max_aggregate, agg, aptr, members, tptr, ibuf + 8,
                                    stream);
             int got[2];
@@ -665,8 +668,13 @@ void amg_hierarchy::build(const amg_csr &A)
             nc = got[1];
             if (passes < 0) throw Error(AMG_ERR_DEVICE, "aggregation made no progress");
             if ((double)nc > opt.stall_ratio * (double)n) {  // coarsening stalled
-                for (void *ptr : std::initializer_list<void *>{agg, aptr, members}) pool.release(ptr);
+                for (void *ptr : std::initializer_list<void *>{agg, members}) pool.release(ptr);
+                if (aptr != cid) pool.release(aptr);
                 return false;
+            }
+            if (aptr == cid) {
+                aptr = pool.alloc<int>(nc + 1);
+                AMG_HIP(hipMemcpyAsync(aptr, cid, sizeof(int) * ((size_t)nc + 1), hipMemcpyDeviceToDevice, stream));
             }
             F.passes = passes;
             F.agg_nat = agg;
@@ -1060,8 +1068,6 @@ void amg_hierarchy::finalize_layout()
         r32 = pool.alloc<float>((size_t)lev[0].n * nr);
         z32 = pool.alloc<float>((size_t)lev[0].n * nr);
     }
-    build_subtree();
-    build_single_unknown();
     const int n = lev[0].n;
     b = pool.alloc<double>((size_t)n * nr);
     x = pool.alloc<double>((size_t)n * nr);
@@ -1085,6 +1091,9 @@ void amg_hierarchy::finalize_layout()
     pool.release(hub_counts);
     for (void *p : drained) pool.release(p);
     drained.clear();
+    // only now what a memory budget may leave out: it takes what the vectors leave over
+    build_subtree();
+    build_single_unknown();
 }
 
 // The longest run of last levels (not the finest) that one workgroup can hold: every
