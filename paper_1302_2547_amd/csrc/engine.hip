@@ -261,8 +261,9 @@ struct Level {
     int *agg_pos = nullptr, *seg_ptr = nullptr, *srp = nullptr;  // all but the coarsest level
     int *cagg = nullptr;                                         // coarse unknown of each entry's column
     int *sci = nullptr;  // columns of the super-rows of P^T A (the same array as ci unless level 0 is natural)
-    // FP64 iterate of the split post-smoothing (levels of at least kSmallLevel rows, those of a batch together)
-    double *xs = nullptr;  // n per column
+    // FP64 iterate of the split post-smoothing, n per column (levels of at least kSmallLevel
+    // rows; smaller ones for a batch, see build_batch_iterates)
+    double *xs = nullptr;
     Sell sell{};             // sliced ELLPACK copy of A for the large-level sweeps (ptr NULL: none)
     double *sell_va = nullptr;
     size_t sell_slots = 0;
@@ -569,6 +570,7 @@ struct amg_hierarchy {
     void build_subtree();
     bool build_star();
     void build_single_unknown();
+    void build_batch_iterates();
     // the inner residual rt = rcf - (alpha1/rho1) v1 of a parent's first step
     template <class T>
     struct RtSource {
@@ -1012,8 +1014,7 @@ void amg_hierarchy::finalize_layout()
                 uperm = nullptr;
                 AMG_TRACE_MSG("layout level 0: natural numbering");
             }
-            if (F.n >= kSmallLevel || (nr > 1 && (size_t)F.n * nr >= (size_t)kSmallLevel))
-                F.xs = pool.alloc<double>((size_t)F.n * nr);
+            if (F.n >= kSmallLevel) F.xs = pool.alloc<double>((size_t)F.n * nr);
             if (F.n < kSmallLevel) {
                 F.cagg = pool.alloc<int>(F.nnz);
                 launch_entry_coarse_column(F.nnz, F.ci, F.agg_pos, F.cagg, stream);
@@ -1094,6 +1095,7 @@ void amg_hierarchy::finalize_layout()
     // only now what a memory budget may leave out: it takes what the vectors leave over
     build_subtree();
     build_single_unknown();
+    build_batch_iterates();
 }
 
 // The longest run of last levels (not the finest) that one workgroup can hold: every
@@ -1188,6 +1190,24 @@ void amg_hierarchy::build_single_unknown()
     launch_single_unknown_weights(F.n, F.rp, F.ci, F.va, F.minv, F.omega, stream);
     F.d_om = dot_buf();
     AMG_TRACE_MSG("level %d: single coarse unknown below, restriction by inner products", L - 1);
+}
+
+// The iterates of the smaller levels whose post-smoothing a batch takes in two launches
+// (launch_post_smooth; in one where there is none).  Not read: on the levels that one
+// workgroup or the star kernel serves, with one column per block, and on the finest
+// level in FP64, whose step always forms the outer inner product.
+void amg_hierarchy::build_batch_iterates()
+{
+    using namespace amg;
+    const size_t nr = (size_t)opt.max_rhs;
+    if (nr < 2) return;
+    for (int l = mixed ? 0 : 1; l < (sub_top ? sub_top : levels() - 1); l++) {
+        Level &F = lev[l];
+        const size_t count = (size_t)F.n * nr;
+        if (F.n >= kSmallLevel || count < (size_t)kSmallLevel || F.A.cb < 2 || F.omega || F.star.n) continue;
+        if (pool.budget && pool.used + count * sizeof(double) > pool.budget) continue;
+        F.xs = pool.alloc<double>(count);
+    }
 }
 
 // Sliced ELLPACK copies of the levels of at least kSmallLevel rows (not the last

@@ -63,3 +63,31 @@ def budgets(amg, make, opt, least):
 @pytest.mark.parametrize("name", sorted(LEAST))
 def test_budget_without_optional_structures(amg, name):
     budgets(amg, *LEAST[name])
+
+
+# the same for several right-hand sides, where the mid-size levels' iterates are optional
+LEAST_BATCH = {
+    "60^3 x 8": (grid(60, 60, 60), {"max_rhs": 8}, 367024888),
+    "60^3 x 8 mixed": (grid(60, 60, 60), {"max_rhs": 8, "precision": 1}, 419577356),
+    "200x200 x 4": (grid(200, 200), {"max_rhs": 4}, 85811564),
+    "graph 20000 x 8": (lambda: inputs.rgg_laplacian(20000, seed=5, weight_range=(0.5, 1.5)), {"max_rhs": 8},
+                        112240144),
+}
+
+
+@pytest.mark.parametrize("name", sorted(LEAST_BATCH))
+def test_budget_of_a_batch(amg, name):
+    budgets(amg, *LEAST_BATCH[name])
+
+
+def test_no_iterates_for_one_column_per_block(amg):
+    """The iterates of 41,000 rows x 8 columns are held only where a batched sweep reads
+    them: not with one column per block."""
+    csr = [dev(v) for v in inputs.grid_laplacian((50, 49, 48), jitter=0.1, seed=9)]
+    held = []
+    for cb in (1, 4):
+        with amg.Hierarchy(*csr, max_rhs=8, batch_cols=cb, autotune=0) as h:
+            rows = [h.level_sizes(l)[0] for l in range(h.num_levels)]
+            held.append(h.memory_bytes)
+    mid = [n for n in rows[1:] if n < 100000 and 8 * n >= 100000]
+    assert mid and held[1] - held[0] == 8 * 8 * sum(mid)
