@@ -1748,17 +1748,21 @@ namespace {
 // The ABI takes device arrays.  Memory the GPU cannot address (pageable host
 // memory) is rejected here, with AMG_ERR_INVALID_ARGUMENT, instead of faulting
 // inside a kernel; device, managed and pinned host memory pass.
-bool device_array(const void *p)
+enum class Memory { none, device, host };  // host: pinned or managed, read over the bus
+Memory memory_of(const void *p)
 {
-    if (!p) return false;
+    if (!p) return Memory::none;
     hipPointerAttribute_t a{};
     if (hipPointerGetAttributes(&a, p) != hipSuccess) {
         (void)hipGetLastError();
-        return false;
+        return Memory::none;
     }
-    return a.type == hipMemoryTypeDevice || a.type == hipMemoryTypeManaged ||
-           (a.type == hipMemoryTypeHost && a.devicePointer != nullptr);
+    if (a.type == hipMemoryTypeDevice) return Memory::device;
+    return a.type == hipMemoryTypeManaged || (a.type == hipMemoryTypeHost && a.devicePointer != nullptr)
+               ? Memory::host
+               : Memory::none;
 }
+bool device_array(const void *p) { return memory_of(p) != Memory::none; }
 
 template <class F>
 amg_status guarded(F &&f)
@@ -2011,6 +2015,8 @@ amg_status amg_spmv(amg_hierarchy *h, int32_t level, const double *x, double *y)
 namespace {
 amg_status kcycle_columns(amg_hierarchy *h, int ncol, const double *r, int ldr, double *z, int ldz)
 {
+    const Memory where = memory_of(r);
+    if (where == Memory::none || !device_array(z)) return AMG_ERR_INVALID_ARGUMENT;
     if (h->kcycle_visits() > amg_hierarchy::kMaxKcycleVisits) return AMG_ERR_UNSUPPORTED;
     return guarded([&]() {
         const Level &F = h->lev[0];
@@ -2023,7 +2029,12 @@ amg_status kcycle_columns(amg_hierarchy *h, int ncol, const double *r, int ldr, 
         const bool short_cycle = h->sub_top == 1 || (h->levels() == 3 && h->lev[1].star.n > 0);
         if (ncol == 1 && !h->mixed && !h->uperm && short_cycle && apart) {
             h->clear_flag();
-            h->kcycle<double>(0, r, z, nullptr, nullptr, 1);
+            const double *in = r;
+            if (where == Memory::host) {  // gathered from by two kernels: one copy over the bus costs less
+                amg::launch_gather(F.n, r, nullptr, h->r, h->stream, 1, F.n, F.n);
+                in = h->r;
+            }
+            h->kcycle<double>(0, in, z, nullptr, nullptr, 1);
         } else {
             const hipGraphExec_t graph =
                 h->graphs_wanted() ? h->captured(&amg_hierarchy::Graphs::k, ncol) : nullptr;
@@ -2051,7 +2062,6 @@ extern "C" {
 amg_status amg_kcycle(amg_hierarchy *h, const double *r, double *z)
 {
     if (!h || !r || !z) return AMG_ERR_INVALID_ARGUMENT;
-    if (!device_array(r) || !device_array(z)) return AMG_ERR_INVALID_ARGUMENT;
     return kcycle_columns(h, 1, r, h->lev[0].n, z, h->lev[0].n);
 }
 
@@ -2060,7 +2070,6 @@ amg_status amg_kcycle_batch(amg_hierarchy *h, int32_t nrhs, const double *R, int
     if (!h || !R || !Z) return AMG_ERR_INVALID_ARGUMENT;
     const int n = h->lev[0].n;
     if (nrhs < 1 || nrhs > h->opt.max_rhs || ldr < n || ldz < n) return AMG_ERR_INVALID_ARGUMENT;
-    if (!device_array(R) || !device_array(Z)) return AMG_ERR_INVALID_ARGUMENT;
     return kcycle_columns(h, nrhs, R, ldr, Z, ldz);
 }
 
