@@ -1680,6 +1680,7 @@ amg_status amg_hierarchy::solve(int ncol, const double *b_user, int ldb, double 
     amg_status st = AMG_ERR_NOT_CONVERGED;
     while (!all_done() && it < opt.max_iters) {
         upload_masks();
+        flag_clear = false;
         if (iteration) {
             AMG_HIP(hipGraphLaunch(iteration, stream));
         } else {
