@@ -126,11 +126,11 @@ void launch_mis_pass(int n, const int *rp, const int *ci, uint64_t *key, uint64_
 void launch_sum_slots(const unsigned *slots, unsigned *out, hipStream_t s);
 // The whole aggregation of a level that fits in one block's LDS: the aggregate of every
 // row, aptr (nc + 1), the members and tptr (nc + 1, exclusive sums of the aggregates'
-// row lengths); info[0] = passes (-1: no progress), info[1] = nc.
+// row lengths); info[0] = passes (-1: no progress, or no aggregation), info[1] = nc.
 bool aggregate_small_fits(int n, int nnz);
 void launch_aggregate_small(int n, int nnz, const int *rp, const int *ci, uint32_t s_l, int cap, int *agg, int *aptr,
                             int *members, int *tptr, int *info, hipStream_t s);
-void launch_centre_flags(int n, const int *owner, int *flag, hipStream_t s);
+void launch_centre_flags(int n, const int *owner, int *flag, int *err, hipStream_t s);
 void launch_assign_aggregates(int n, const int *owner, const int *cid, int *agg, int *centre_of, hipStream_t s);
 void launch_member_counts(int nc, const int *rp, const int *ci, const int *owner, const int *centre_of, int *size,
                           int *pairs, hipStream_t s);

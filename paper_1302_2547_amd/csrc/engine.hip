@@ -714,9 +714,12 @@ void amg_hierarchy::build(const amg_csr &A)
             }
             AMG_TRACE_MSG("level %d: %d aggregation passes", l, passes);
             // Sec. 5.1: aggregates numbered by increasing coarse-vertex index
-            launch_centre_flags(n, owner, cid, stream);
+            launch_centre_flags(n, owner, cid, ibuf, stream);
             scan(cid, cid, n, ibuf + 3, scan_tmp);
-            nc = read_int(ibuf + 3);
+            int got[4];
+            to_host(got, ibuf, 4);
+            if (got[0] != 0) throw Error(AMG_ERR_DEVICE, "no aggregation: asymmetric pattern");
+            nc = got[3];
             if ((double)nc > opt.stall_ratio * (double)n) return false;  // coarsening stalled
             F.passes = passes;
             F.agg_nat = pool.alloc<int>(n);

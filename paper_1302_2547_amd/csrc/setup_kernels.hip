@@ -371,10 +371,16 @@ __global__ void __launch_bounds__(kDoneSlots) k_sum_slots(const unsigned *__rest
 
 // ------------------------------------------------------------------ numbering (Sec. 5.1)
 
-__global__ void __launch_bounds__(kBlock) k_centre_flags(int n, const int *__restrict__ owner, int *__restrict__ flag)
+// *err = 1 when a row has no owner that is a coarse vertex: claims of an asymmetric
+// pattern can overlap and then count as many rows as there are with one left over.
+__global__ void __launch_bounds__(kBlock) k_centre_flags(int n, const int *__restrict__ owner, int *__restrict__ flag,
+                                                         int *__restrict__ err)
 {
     const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i < n) flag[i] = owner[i] == i ? 1 : 0;
+    if (i >= n) return;
+    const int o = owner[i];
+    if (o < 0 || owner[o] != o) *err = 1;
+    flag[i] = o == i ? 1 : 0;
 }
 
 __global__ void __launch_bounds__(kBlock) k_assign_aggregates(int n, const int *__restrict__ owner,
@@ -512,7 +518,7 @@ __global__ void __launch_bounds__(kAggThreads) k_aggregate_small(int n, int nnz,
                                                                  int *__restrict__ tptr_out, int *__restrict__ info)
 {
     extern __shared__ __align__(16) char lds[];
-    __shared__ int sh[kAggThreads / kWave], nhub;
+    __shared__ int sh[kAggThreads / kWave], nhub, lost;
     __shared__ unsigned done;
     const SmallLayout L = small_layout(n, nnz);
     uint64_t *key = reinterpret_cast<uint64_t *>(lds + L.key), *m1 = reinterpret_cast<uint64_t *>(lds + L.m1);
@@ -521,7 +527,7 @@ __global__ void __launch_bounds__(kAggThreads) k_aggregate_small(int n, int nnz,
     constexpr int G = kAggLanes;
     const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave, sub = t % G, gbase = lane - sub;
     const uint64_t gmask = ((1ull << G) - 1ull) << gbase;
-    if (t == 0) nhub = 0;
+    if (t == 0) nhub = lost = 0;
     __syncthreads();
     for (int e = t; e < nnz; e += kAggThreads) ci[e] = (uint16_t)ci_in[e];
     for (int i = t; i < n; i += kAggThreads) {
@@ -618,17 +624,19 @@ __global__ void __launch_bounds__(kAggThreads) k_aggregate_small(int n, int nnz,
         processed += d;
         if (d == 0 || processed >= (unsigned)n) break;  // every pass processes a vertex, or the level is in error
     }
-    if (processed != (unsigned)n) {
-        if (t == 0) info[0] = -1;
-        return;
-    }
     int *cid = reinterpret_cast<int *>(lds + L.m1);
     int *size = reinterpret_cast<int *>(lds + L.key), *pairs = size + n;
     for (int i = t; i < n; i += kAggThreads) {
-        cid[i] = owner[i] == i ? 1 : 0;
+        const int o = owner[i];
+        if (o >= n || owner[o] != o) lost = 1;  // as k_centre_flags
+        cid[i] = o == i ? 1 : 0;
         size[i] = pairs[i] = 0;
     }
     __syncthreads();
+    if (lost || processed != (unsigned)n) {
+        if (t == 0) info[0] = -1;
+        return;
+    }
     const int nc = lds_scan(cid, n, sh);
     for (int i = t; i < n; i += kAggThreads) {
         const int I = cid[owner[i]];
@@ -1747,9 +1755,9 @@ void launch_aggregate_small(int n, int nnz, const int *rp, const int *ci, uint32
                                                                          tptr, info);
     AMG_HIP(hipGetLastError());
 }
-void launch_centre_flags(int n, const int *owner, int *flag, hipStream_t s)
+void launch_centre_flags(int n, const int *owner, int *flag, int *err, hipStream_t s)
 {
-    k_centre_flags<<<grid_for(n), kBlock, 0, s>>>(n, owner, flag);
+    k_centre_flags<<<grid_for(n), kBlock, 0, s>>>(n, owner, flag, err);
     AMG_HIP(hipGetLastError());
 }
 
