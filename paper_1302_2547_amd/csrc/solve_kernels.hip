@@ -284,6 +284,7 @@ __device__ inline void visit_rows(const Rows &R, Prologue prologue, Pre pre, Lat
             double s = 0.0;
 #pragma unroll
             for (int u = 0; u < kChunk / kBlock; u++) {
+#pragma clang fp contract(off)  // the sums of k_smooth_finish_mm<SMALL> have the same bits
                 const int p = ch.beg + (int)threadIdx.x + u * kBlock;
                 const double t = term(p < ch.end ? p : ch.end - 1);
                 s += p < ch.end ? t : 0.0;
@@ -664,6 +665,33 @@ __global__ void __launch_bounds__(kBlock) k_theta_gate(DotRef rcrc, DotRef rtrt,
     if (threadIdx.x == 0) gate[blockIdx.y] = run && !(v[1] < theta2 * v[0]) ? 1 : 0;
 }
 
+// A product rounded by itself.  (The compiler contracts HIP's __dmul_rn and __dadd_rn
+// into fused multiply-adds as it does plain operators.)
+__device__ __forceinline__ double mul_alone(double a, double b)
+{
+#pragma clang fp contract(off)
+    return a * b;
+}
+// The pieces of the post-smoothing step, as all of its forms take them (one launch, two,
+// one sweep, a column alone or in a batch, gated or not): rounded step by step, nothing
+// left to the compiler's contraction, so that all forms give the same bits.
+//   the coarse value a1 c1 (+ a2 c2) of a row, the prolonged iterate x = M^-1 r + e, and
+//   the smoothed one x + M^-1 (r - (A x))
+__device__ __forceinline__ double combined(double a1, double c1, double a2, double c2, bool two)
+{
+    return two ? __fma_rn(a1, c1, mul_alone(a2, c2)) : mul_alone(a1, c1);
+}
+template <int MODE, class T>
+__device__ inline double coarse_value(const KCoef &c, const T *edirect, const T *c1, const T *c2, int J)
+{
+    if (MODE == 0) return (double)edirect[J];
+    if (MODE == 1) return mul_alone(c.a1, (double)c1[J]);
+    const double v1 = (double)c1[J], v2 = (double)c2[J];
+    return combined(c.a1, v1, c.a2, v2, c.two);
+}
+__device__ inline double prolonged_iterate(double minv, double r, double e) { return __fma_rn(minv, r, e); }
+__device__ inline double smoothed(double x, double minv, double r, double ax) { return __fma_rn(minv, r - ax, x); }
+
 // Prolongation + post-smoothing: x = M^-1 r + P e (the pre-smoothed iterate plus
 // the coarse correction) is formed on the fly for every column (cagg[p], when
 // given, is the coarse unknown of column ci[p] stored per entry: on small,
@@ -697,14 +725,13 @@ __global__ void __launch_bounds__(kBlock) k_post_smooth(Rows R, const int *__res
     double a1 = 0.0, a2 = 0.0;
     bool two = MODE == 2;  // a constant unless GATE
     __shared__ double e_sh[MODE == 3 ? kInlineCoarse : 1];
-    // rounded step by step, so that the gated and the ungated kernel give the same
-    // bits; both loads issue unconditionally (a skipped second step's c2 is not used)
+    // both loads issue unconditionally (a skipped second step's c2 is not used)
     auto corr = [&](int J) -> double {
         if (MODE == 0) return (double)edirect[J];
         if (MODE == 3) return e_sh[J];
-        if (MODE == 1) return __dmul_rn(a1, (double)c1[J]);
+        if (MODE == 1) return mul_alone(a1, (double)c1[J]);
         const double v1 = (double)c1[J], v2 = (double)c2[J];
-        return two ? __fma_rn(a1, v1, __dmul_rn(a2, v2)) : __dmul_rn(a1, v1);
+        return combined(a1, v1, a2, v2, two);
     };
     struct Pre {
         double mr, rr, wd;
@@ -749,11 +776,11 @@ __global__ void __launch_bounds__(kBlock) k_post_smooth(Rows R, const int *__res
         [&](const Pre &v) { return Late{v.mr, v.rr, v.wd, corr(v.J)}; },
         [&](int p) {
             const int t = ci[p];
-            return (double)va[p] * ((double)minv[t] * (double)r[t] + corr(CAGG ? cagg[p] : agg_pos[t]));
+            return (double)va[p] *
+                   prolonged_iterate((double)minv[t], (double)r[t], corr(CAGG ? cagg[p] : agg_pos[t]));
         },
         [&](int row, double s, int k, const Late &v) {
-            const double x = v.mr * v.rr + v.cj;
-            const double o = x + v.mr * (v.rr - s);
+            const double o = smoothed(prolonged_iterate(v.mr, v.rr, v.cj), v.mr, v.rr, s);
             xout[row] = (T)o;
             if (DOT) {
                 if (k < 0) dsum[0] += o * v.wd;
@@ -762,21 +789,6 @@ __global__ void __launch_bounds__(kBlock) k_post_smooth(Rows R, const int *__res
         });
     if (DOT) store_partials<1>(dsum, part);
 }
-
-// The prolonged iterate x = M^-1 r + (P e) of one row and its coarse value e, as the
-// two-launch and the one-sweep post-smoothing of large levels form it: rounded step
-// by step (explicit fused multiply-adds, no contraction left to the compiler), so
-// both forms produce the same bits.
-template <int MODE, class T>
-__device__ inline double coarse_value(const KCoef &c, const T *edirect, const T *c1, const T *c2, int J)
-{
-    if (MODE == 0) return (double)edirect[J];
-    if (MODE == 1) return __dmul_rn(c.a1, (double)c1[J]);
-    const double v1 = (double)c1[J], v2 = (double)c2[J];
-    return c.two ? __fma_rn(c.a1, v1, __dmul_rn(c.a2, v2)) : __dmul_rn(c.a1, v1);
-}
-__device__ inline double prolonged_iterate(double minv, double r, double e) { return __fma_rn(minv, r, e); }
-__device__ inline double smoothed(double x, double minv, double r, double ax) { return __fma_rn(minv, __dsub_rn(r, ax), x); }
 
 // Large levels split the same step in two launches, so that each entry gathers one
 // value instead of five (the fused form recomputes x_t = M^-1 r_t + (P e)_t for every
@@ -834,7 +846,7 @@ __global__ void __launch_bounds__(kBlock) k_smooth_finish(Rows R, const int *__r
         [&](int row) { return Pre{(double)minv[row], (double)r[row], x[row], DOT ? (double)wdot[row] : 0.0}; },
         AMG_SAME, [&](int p) { return (double)va[p] * x[ci[p]]; },
         [&](int row, double s, int k, const Pre &v) {
-            const double o = v.xr + v.mr * (v.rr - s);
+            const double o = smoothed(v.xr, v.mr, v.rr, s);
             xout[row] = (T)o;
             if (DOT) {
                 if (k < 0) dsum[0] += o * v.wd;
@@ -1017,7 +1029,7 @@ __global__ void __launch_bounds__(kBlock) k_smooth_finish_mm(Rows R, const int *
     double d[CB][1] = {};
     auto row_done = [&](int row, int k, double s, int hub) {
         const size_t o = col(k) * n + row;
-        const double out = x[o] + (double)minv[row] * ((double)r[o] - s);
+        const double out = smoothed(x[o], (double)minv[row], (double)r[o], s);
         xout[o] = (T)out;
         if (DOT) {
             const double t = out * (double)wdot[o];
@@ -1039,8 +1051,7 @@ __global__ void __launch_bounds__(kBlock) k_smooth_finish_mm(Rows R, const int *
 #pragma unroll
             for (int k = 0; k < CB; k++) {
                 const double xj = x[col(k) * n + j];
-                // as the one-launch form of small levels sums a chunk
-                s[k] = SMALL ? __dadd_rn(s[k], __dmul_rn(a, xj)) : s[k] + a * xj;
+                s[k] = SMALL ? s[k] + mul_alone(a, xj) : s[k] + a * xj;  // as visit_rows sums a chunk
             }
         },
         [&](int row, const Chunk &ch, double (&s)[CB]) {
