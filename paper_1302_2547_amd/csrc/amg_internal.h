@@ -59,8 +59,8 @@ struct Rows {
     double *chunk_sum;
     unsigned *arrive;
     // right-hand sides served by one block in batched sweeps of levels of at least
-    // kSmallLevel rows (1: one column per block; 2, 4, 8: each entry loaded once for
-    // that many columns)
+    // kSmallLevel rows, and in the two-launch post-smoothing of smaller ones (1: one column
+    // per block; 2, 4, 8: each entry loaded once for that many columns)
     int cb;
 };
 constexpr int kMaxColumnsPerBlock = 8;
@@ -305,9 +305,10 @@ DotRef launch_inner_residual_theta(int n, const T *rc, const T *v1, KDots kd, T 
 // 1: e = (alpha1/rho1) c1; 2: e = a1 c1 + a2 c2; 3: e = ainv * edirect, a dense
 // coarsest solve of size nc <= kInlineCoarse done in the kernel); returns
 // (out, wdot) if wdot.  nc is the coarse level's size (the leading dimension of
-// edirect, c1, c2).  xtmp (FP64, n per right-hand side, or NULL): on levels of at
-// least kSmallLevel rows the step is then split in two launches through it, the
-// second served from the sliced ELLPACK copy sl (values sva) when given.  second
+// edirect, c1, c2).  xtmp (FP64, n per right-hand side, or NULL): the step is split in
+// two launches through it on levels of at least kSmallLevel rows (the second served from
+// the sliced ELLPACK copy sl, values sva, when given), and for a batch of at least
+// kSmallLevel values without wdot, where R.cb > 1.  second
 // (mode 2, or NULL): the gate of the second inner step; a column whose gate is 0
 // takes the mode 1 correction.
 template <class T>
@@ -382,7 +383,8 @@ int subtree_lds_limit();
 // need[d], d = 1 .. count - 1 (device array) of the `count` last levels
 void launch_subtree_needs(const SubtreeSource &P, int count, SubtreeNeed *need, hipStream_t s);
 // The deepest subtree that fits (levels >= 2 in S), from the needs of the `count`
-// last levels (n: their sizes, coarsest first).  S's arrays are taken from alloc(bytes).
+// last levels (n: their sizes, coarsest first).  S's array pointers stay unset
+// (launch_subtree_pack).
 bool layout_subtree(int count, const int *n, const SubtreeNeed *need, const CoarseSolve &cs, int value_bytes,
                     int lds_limit, Subtree &S);
 size_t subtree_bytes(const Subtree &S, int value_bytes);

@@ -1378,8 +1378,10 @@ __device__ __forceinline__ void star_sums(double (&v)[4 * N], int set)
 // the sums of the second step's input follow from the first step's by
 // rt = r - q y).  Every row costs four loads (r, M^-1, d, u); what bounds the kernel is
 // one compute unit's fetch of them.  4,128 rows in FP64: 8.4 us, where a form that kept the
-// entries in slots and gathered from LDS took 15.3; 6,898 rows, 8 columns in FP32: 13.7 us.
-// A larger star stays with k_post_direct: more than eight rows per thread do not fit.
+// entries in slots and gathered from LDS took 15.3; 6,898 rows, 8 columns in FP32: 13.7 us,
+// of which the spills of eight rows per thread are a part (16 registers in FP64, 34 in
+// FP32; none with five).  A larger star stays with k_post_direct: more rows per thread do
+// not fit.  The hub's row is taken from the leaves' column: A is symmetric.
 // R: rows per thread; EXTRA: there are leaf-leaf entries, whose columns are exchanged
 // through LDS for each of the four products.
 template <class T, int R, bool EXTRA>
@@ -2109,7 +2111,13 @@ DotRef launch_post_smooth(Rows R, const int *ci, const T *va, const T *minv, con
     // on at which its columns together are as many rows: the one-launch form gathers
     // five values per entry and column and reads the matrix once per column.  Measured
     // with 8 columns in FP32 storage over the 76,580-, 24,532- and 13,928-row levels of
-    // the 100^3 grid: 33.5 us a visit on average in one launch, 18.4 in two.
+    // the 100^3 grid: 33.5 us a visit on average in one launch, 18.4 in two.  K-cycles in us
+    // with the line at 30,000 / here / at 300,000 / no split: 100^3, FP64, 2 columns 2,329 /
+    // 2,335 / 2,331 / 2,328; 8 columns 3,996 / 3,995 / 4,376 / 4,484; 32 columns (levels of
+    // 3,125 rows on) 11,172 / 11,196 / 11,178 / 13,554; 41x37x29, FP32, 32 columns 753 / 751
+    // / 778 / 978; 181x173, FP64, 2 columns 219 / 215 / 220 / 219, 32 columns 507 / 507 /
+    // 494 / 577; a graph of 300,000 points, FP64, 8 columns 2,397 / 2,398 / - / 2,481, 32
+    // columns 3,709 / 3,707 / - / 4,176.
     const bool batch = ncol > 1 && R.cb > 1 && !dot && (int64_t)R.n * ncol >= kSmallLevel;
     if (xtmp && (batch || (!cagg && R.n >= kSmallLevel)) && mode >= 0 && mode <= 2) {
         const dim3 g1(grid_for(R.n, 1 << 16), ncol);

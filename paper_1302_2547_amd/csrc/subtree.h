@@ -41,25 +41,6 @@ __device__ __forceinline__ void sub_totals(const double *part, double (&v)[4])
     for (int d = 0; d < 4; d++) v[d] = lane_value(t, d);
 }
 
-// Sum over entries b, b + step, ... < e of term(p), kSubUnroll in flight (clamped
-// indices, entries past the end add nothing).
-template <class Term>
-__device__ __forceinline__ double sub_span(int b, int e, int step, Term term)
-{
-    double s = 0.0;
-    for (int p = b; p < e; p += kSubUnroll * step) {
-        double t[kSubUnroll];
-#pragma unroll
-        for (int u = 0; u < kSubUnroll; u++) {
-            const int q = p + u * step;
-            t[u] = term(q < e ? q : p);
-        }
-#pragma unroll
-        for (int u = 0; u < kSubUnroll; u++) s += p + u * step < e ? t[u] : 0.0;
-    }
-    return s;
-}
-
 // LDS, in bytes at compile-time places (the offsets are part of the instructions, and
 // no address is held in registers): the exact solve's residual and solution, then the
 // vectors g, c1 and c2 of levels 1, 2, ...  A level of K slots per thread has room for

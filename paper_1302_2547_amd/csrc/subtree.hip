@@ -8,16 +8,17 @@
 // correction of the top one runs in one workgroup per right-hand side (k_subtree):
 // every pass of the recursion below -- about 9 for each visit of a level -- is a
 // sweep between two block barriers instead of a launch.  What bounds it is the chain of
-// those passes: the instructions of one wavefront, LDS latency and cross-lane sums (450
-// to 900 clocks a pass).  Hence 512 threads and no more rows per thread than needed, rows
-// packed by length (2^c lanes, four entries a lane), LDS places known at compile time, and
-// one body of code for both inner steps (a miss of the instruction cache costs as much as
-// an LDS read, and the code of six levels is about its size).
+// those passes: the instructions of one wavefront, LDS latency and cross-lane sums, 450
+// to 900 clocks a pass.  On a top level of four slots per thread, whose code is larger
+// than the instruction cache holds beside the other levels', a pass takes 4,000 to 8,000.
+// Hence 512 threads and no more rows per thread than needed, rows packed by length (2^c
+// lanes, four entries a lane), LDS places known at compile time, and one body of code for
+// both inner steps.
 //
 // Measured: 38.3 us for the levels of 971, 286, 108 and 37 rows under the 1003x997 grid,
 // 21.4 us for 990, 191 and 50; the 20 launches that the first replaces took about 110 us.
-// A solve of that grid went from 58.3 to 22.4 ms, a K-cycle of a 33x31 grid
-// from 97 to 57 us.
+// A solve of that grid went from 58.8 to 22.2 ms, a K-cycle of a 33x31 grid
+// from 102 to 38 us (with the cycle on the caller's vectors).
 #include <algorithm>
 
 #include "subtree.h"
@@ -286,8 +287,13 @@ bool layout_subtree(int count, const int *n, const SubtreeNeed *need, const Coar
     // The top level may have several slots per thread, the ones below it one: a level is
     // swept twice as often as the one above it, and more than four slots (or two on two
     // levels) do not fit the registers.  Every level more that fits is taken: each halves
-    // the launches of a K-cycle, and a pass here (450 to 900 clocks) is shorter than a
-    // launch (4 to 5 us).
+    // the launches of a K-cycle.  That pays also where its four slots make a pass as long
+    // as a launch (4,000 to 8,000 clocks; 4 to 5 us): the levels above stop at a lower
+    // count of visits.  K-cycle with a top level of up to 4 / 2 / 1 slots per thread, in
+    // us: 45x45 46 / 77 / 76, 131x67 110 / 130 / 134, 1003x997 1,278 / 1,565 / 1,561, graph
+    // of 5,000 points 59 / 91 / 92, of 150,000 1,257 / 1,401 / 1,402; top level of two
+    // slots: 33x31 41 / 41 / 70, 41x37x29 395 / 397 / 565, 300,000 points 1,985 / 1,973 /
+    // 2,728.  No problem of these is slower with the wider level.
     int top = 0;
     for (int d = 1; d < count && d <= kSubtreeDepth; d++) {
         if (need[d].waves <= 4 * kSubWaves) top = d;
