@@ -95,7 +95,7 @@ def check(amg, csr, columns=1, **opt):
 
 
 HELD = {
-    # one to six levels above the coarsest, on every count of slots per thread
+    # two levels above the coarsest on two and four slots per thread, six on one (9x9: none)
     "grid_9x9": (lambda: inputs.grid_laplacian((9, 9), jitter=0.2, seed=1), {}),
     "grid_25x24": (lambda: inputs.grid_laplacian((25, 24), jitter=0.2, seed=1), {}),
     "grid_45x45": (lambda: inputs.grid_laplacian((45, 45), jitter=0.2, seed=1), {}),
@@ -104,12 +104,12 @@ HELD = {
     # more small levels than one workgroup takes
     "path_2000_pairs": (lambda: inputs.grid_laplacian((2000,), jitter=0.2, seed=1),
                         {"coarsest_size": 2, "max_aggregate": 2}),
-    # rows of every group width, and one longer than a wavefront's slots
+    # rows of 1, 2, 4, 16 and 64 lanes (dense_200: two levels, nothing held)
     "dense_200": (lambda: inputs.random_graph_laplacian(200, 0.4, 5, False), {"coarsest_size": 8}),
     "hub_40": (lambda: hub_and_grid(40, 40), {}),
     "hub_257": (lambda: hub_and_grid(40, 257), {}),
     "hub_700": (lambda: hub_and_grid(40, 700), {"max_aggregate": 3}),
-    # decoupled coarsest unknowns (isolated vertices), and a single one below a star
+    # isolated vertices (graph_sparse: more than a workgroup takes), and a star on its own
     "graph_3000": (lambda: inputs.rgg_laplacian(3000, seed=5, weight_range=(0.5, 1.5)), {}),
     "graph_sparse": (lambda: inputs.rgg_laplacian(4000, mean_degree=3.0, seed=5), {}),
     "star_600": (lambda: star_graph(600, 5), {"coarsest_size": 1}),
@@ -161,7 +161,8 @@ def test_coarsest_inverse(amg, n):
     h.close()
 
 
-# mid-size levels of a batch are smoothed in two launches, those of a single column in one
+# mid-size levels of a batch are smoothed in two launches (here level 1 from three columns
+# on), those of a single column in one
 @pytest.mark.parametrize("columns", [2, 5, 8])
 @pytest.mark.parametrize("precision", [0, 1])
 def test_batched_mid_level_bits(amg, columns, precision):
