@@ -4,9 +4,9 @@
 // Device memory is owned by one pool per hierarchy; a failed setup releases
 // everything it allocated.  All work is ordered on one HIP stream; the host
 // waits on it only where it needs a value: the per-pass count of processed
-// vertices, level sizes, the small levels it lays out itself (the coarsest
-// level's split solve, the level above a single coarse unknown), the lane-count
-// timings of the first solve, and the outer residual norm.
+// vertices, level sizes, the counts of hub rows, the small coarsest level whose
+// split solve it lays out itself, what the one-workgroup and star layouts need,
+// the lane-count timings of the first solve, and the outer residual norm.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -217,6 +217,17 @@ struct Pool {
         used += bytes;
         peak = std::max(peak, used);
         return static_cast<T *>(p);
+    }
+    // For what can be left out: NULL where the budget or the device has no room.
+    template <class T>
+    T *try_alloc(size_t count)
+    {
+        try {
+            return alloc<T>(count);
+        } catch (const Error &e) {
+            if (e.status != AMG_ERR_OUT_OF_MEMORY) throw;
+            return nullptr;
+        }
     }
     void release(void *p)
     {
@@ -1122,8 +1133,8 @@ void amg_hierarchy::build_subtree()
     }
     const int count = (int)n.size();
     if (count < 2) return;
-    if (pool.budget && pool.used + sizeof(SubtreeNeed) * (kSubtreeDepth + 1) > pool.budget) return;
-    SubtreeNeed *dneed = pool.alloc<SubtreeNeed>(kSubtreeDepth + 1);
+    SubtreeNeed *dneed = pool.try_alloc<SubtreeNeed>(kSubtreeDepth + 1);
+    if (!dneed) return;
     launch_subtree_needs(P, count, dneed, stream);
     SubtreeNeed need[kSubtreeDepth + 1];
     to_host(need, dneed, kSubtreeDepth + 1);
@@ -1136,10 +1147,12 @@ void amg_hierarchy::build_subtree()
         sub = Subtree{};
         return;
     }
-    const size_t bytes = subtree_bytes(sub, mixed ? 4 : 8);
-    if (pool.budget && pool.used + bytes > pool.budget) return;
+    char *base = pool.try_alloc<char>(subtree_bytes(sub, mixed ? 4 : 8));
+    if (!base) {
+        sub = Subtree{};
+        return;
+    }
     sub.nu = opt.kcycle_inner;
-    char *base = pool.alloc<char>(bytes);
     if (mixed) launch_subtree_pack<float>(sub, P, base, stream);
     else launch_subtree_pack<double>(sub, P, base, stream);
     sub_top = L + 1 - sub.levels;
@@ -1161,8 +1174,9 @@ bool amg_hierarchy::build_star()
     const size_t value = mixed ? sizeof(float) : sizeof(double);
     const size_t rows = ((size_t)F.n * value + 15) / 16 * 16;
     const size_t bytes = 2 * rows + sizeof(StarExtra) + sizeof(StarInfo);
-    if (F.n < 3 || F.n > kStarMaxRows || (pool.budget && pool.used + bytes > pool.budget)) return false;
-    char *at = pool.alloc<char>(bytes);
+    if (F.n < 3 || F.n > kStarMaxRows) return false;
+    char *at = pool.try_alloc<char>(bytes);
+    if (!at) return false;
     StarExtra *ext = reinterpret_cast<StarExtra *>(at + 2 * rows);
     StarInfo *dinfo = reinterpret_cast<StarInfo *>(ext + 1), info{};
     if (mixed)
@@ -1208,8 +1222,7 @@ void amg_hierarchy::build_batch_iterates()
         Level &F = lev[l];
         const size_t count = (size_t)F.n * nr;
         if (F.n >= kSmallLevel || count < (size_t)kSmallLevel || F.A.cb < 2 || F.omega || F.star.n) continue;
-        if (pool.budget && pool.used + count * sizeof(double) > pool.budget) continue;
-        F.xs = pool.alloc<double>(count);
+        F.xs = pool.try_alloc<double>(count);
     }
 }
 
