@@ -94,7 +94,8 @@ typedef struct {
                                 /* launches (the iterate stored), 1 = one sweep forming the */
                                 /* iterate per entry, -1 = timed at the first solve with    */
                                 /* autotune (default; two launches without).  Same result.  */
-    int32_t batch_cols;         /* batched solves on levels >= 100k rows kept in CSR: the    */
+    int32_t batch_cols;         /* batched solves on levels >= 100k rows kept in CSR (and in */
+                                /* post-smoothing of smaller ones from 100k values on): the  */
                                 /* right-hand sides one block serves, each entry loaded     */
                                 /* once for all of them (CSR SpMM): 1, 2, 4 or 8; 0 = timed */
                                 /* at the first batched solve with autotune, else 4 (def.). */
